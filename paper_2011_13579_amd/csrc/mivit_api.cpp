@@ -49,7 +49,7 @@ hipError_t launch_fwd_r4q(const DevCode* codes, const Item* items, const SplitUn
                           int32_t* end_out, int32_t* item_end, int32_t* counter, int grid_limit,
                           R4Bound* bounds, int64_t* last_m, const SplitUnit* split, int n_split,
                           int64_t* rep_m0, hipStream_t st);
-hipError_t launch_tb_r4p(int K, const Item* items, const int2* pairs, int n_pairs,
+hipError_t launch_tb_r4p(int kind_k, const Item* items, const int2* table, int n_waves,
                          const uint64_t* surv, const int32_t* item_end, uint32_t* bits, int warm,
                          hipStream_t st);
 hipError_t launch_fwd_r4_mfma(const MfmaGroups& G, const DevCode* codes, const Item* items,
@@ -80,14 +80,15 @@ enum : int {
   kLayoutRotByte = 4,  // per 8 stages, 2^(K-1) bytes of positions (wide kernel)
   kLayoutNatR8 = 5,
 };
-constexpr int kWarmStages = 64;  // speculative traceback warm-up
-// The packed radix-4 traceback runs one wavefront per frame pair, so one
-// mis-started segment (whose boundary state disagrees with the exact lane
-// above) re-chases a whole segment while the rest of the grid idles: a
-// longer warm-up that makes repairs rare costs less than the repairs
-// (4096 x 8192 K=7 frames at 3 dB: 64 stages 0.095 ms, 80 0.085, 96 0.073,
-// 112 0.073, 128 0.076).  The radix-2 tracebacks measured best at 64.
-constexpr int kWarmStagesR4P = 96;
+constexpr int kWarmStages = 64;  // speculative traceback warm-up, generic layouts
+
+// Which rotating layout the segmented traceback reads, or -1 (generic).
+int tb_kind(int layout) {
+  return layout == kLayoutRotR2 ? kTbWords
+         : layout == kLayoutRotByte ? kTbBytes
+         : layout == kLayoutRot4P ? kTbPairs
+                                  : -1;
+}
 // rotating forward kernel: its MODE template argument per plan variant.
 // Variant 0 (MODE 2): all exchanges in the VALU (DPP, permlane swaps);
 // variant 1 (MODE 0): both previous-state metrics via DPP/LDS swizzles;
@@ -138,8 +139,6 @@ struct PlanGroup {
   int count;
   int wave_off;  // rotating kernels: first entry of the group in the wave table
   int n_waves;
-  int pair_off;  // packed radix-4 kernel: first entry in the traceback pair table
-  int n_pairs;
   int counter;   // persistent launch: index of the group's work counter, else -1
 };
 
@@ -154,7 +153,6 @@ struct Part {
   int32_t* d_item_end = nullptr;
   uint64_t* d_surv = nullptr;
   int2* d_waves = nullptr;  // rotating kernels: (first item, count) per wavefront
-  int2* d_pairs = nullptr;  // packed radix-4 traceback: (first item, count) per frame pair
   int32_t* d_counters = nullptr;
   int n_counters = 0;
   // packed radix 4: work units (parts of entries), split entries' part-0
@@ -169,6 +167,9 @@ struct Part {
   int64_t* d_rep_m0 = nullptr;
   SplitUnit* d_rep_units = nullptr;
   int32_t* d_rep_count = nullptr;
+  int2* d_tb = nullptr;  // rotating layouts: traceback wavefronts, then frame pairs
+  int n_tb = 0;
+  int tb_warm = 0;  // its warm-up, in blocks of 32 stages
   MfmaGroups mg{};  // dragonfly groups (matrix-core radix-4 kernel)
 };
 
@@ -250,7 +251,6 @@ void free_part(Part& q) {
   (void)hipFree(q.d_item_end);
   (void)hipFree(q.d_surv);
   (void)hipFree(q.d_waves);
-  (void)hipFree(q.d_pairs);
   (void)hipFree(q.d_counters);
   (void)hipFree(q.d_units);
   (void)hipFree(q.d_split);
@@ -260,6 +260,7 @@ void free_part(Part& q) {
   (void)hipFree(q.d_rep_m0);
   (void)hipFree(q.d_rep_units);
   (void)hipFree(q.d_rep_count);
+  (void)hipFree(q.d_tb);
   q = Part();
 }
 
@@ -402,7 +403,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   g.beta = c.beta;
   g.first = 0;
   g.count = (int)items.size();
-  g.wave_off = g.n_waves = g.pair_off = g.n_pairs = 0;
+  g.wave_off = g.n_waves = 0;
   g.counter = -1;
   for (size_t k = 0; k < items.size(); ++k) {
     items[k].slot = (int32_t)k;
@@ -439,7 +440,6 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
     if (packed) {
       for (const int2& w : waves)
         for (int s = 0; s < w.y; s += 2) pairs.push_back(make_int2(w.x + s, std::min(2, w.y - s)));
-      g.n_pairs = (int)pairs.size();
       // work units: whole entries, or parts of entries in time.  The batch
       // is to fill about kSplitWavesPerSimd wavefronts per SIMD: with slots
       // such wavefront places and I iterations over all entries, an entry
@@ -544,6 +544,32 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
       }
     }
   }
+  // traceback wavefronts of the rotating layouts
+  std::vector<int2> tbw;
+  if (const int kind = tb_kind(g.layout); kind >= 0) {
+    const int n_ent = kind == kTbPairs ? (int)pairs.size() : (int)items.size();
+    auto n_out = [&](int k) { return items[kind == kTbPairs ? pairs[k].x : k].n_out; };
+    int64_t blocks = 0;
+    for (int k = 0; k < n_ent; ++k) blocks += ((int64_t)n_out(k) + 31) / 32;
+    int dev = 0, cus = 256;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      cus = 256;
+    const TbShape shape = tb_shape(kind, c.K, cus, blocks);
+    q.tb_warm = shape.warm;
+    for (int k = 0; k < n_ent; ++k) {
+      if (n_out(k) <= 0) continue;
+      const int l = tb_log2_lanes(kind, n_out(k), shape.per);
+      const int n = tbw.empty() ? 0 : tbw.back().y & 0xFFFF;
+      if (n > 0 && tbw.back().y >> 16 == l && tbw.back().x + n == k &&
+          n < (1 << tb_max_log2(kind)) >> l)
+        tbw.back().y++;
+      else
+        tbw.push_back(make_int2(k, 1 | l << 16));
+    }
+    q.n_tb = (int)tbw.size();
+    tbw.insert(tbw.end(), pairs.begin(), pairs.end());
+  }
   // survivor memory, 16-byte aligned per item (per frame pair when packed)
   int64_t words_total = 0;
   for (size_t k = 0; k < items.size(); ++k) {
@@ -567,7 +593,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   q.items = items;
   hipError_t e = upload(&q.d_items, items.data(), items.size());
   if (e == hipSuccess) e = upload(&q.d_waves, waves.data(), waves.size());
-  if (e == hipSuccess) e = upload(&q.d_pairs, pairs.data(), pairs.size());
+  if (e == hipSuccess) e = upload(&q.d_tb, tbw.data(), tbw.size());
   if (e == hipSuccess && !items.empty())
     e = hipMalloc((void**)&q.d_item_end, items.size() * sizeof(int32_t));
   if (e == hipSuccess && !items.empty())
@@ -636,12 +662,12 @@ hipError_t part_forward(const mivit_plan* p, const Part& q, const void* llr, voi
 
 hipError_t part_traceback(const mivit_plan* p, const Part& q, uint32_t* bits, hipStream_t st) {
   for (const PlanGroup& g : q.groups) {
+    const int kind = tb_kind(g.layout);
     hipError_t e =
-        g.layout == kLayoutRot4P
-            ? launch_tb_r4p(g.K, q.d_items, q.d_pairs + g.pair_off, g.n_pairs, q.d_surv,
-                            q.d_item_end, bits, kWarmStagesR4P, st)
-            : launch_tb_seg(g.layout, p->d_codes, q.d_items + g.first, g.count, q.d_surv,
-                            q.d_item_end, bits, kWarmStages, st);
+        kind >= 0 ? launch_tb_r4p(16 * kind + g.K, q.d_items, q.d_tb, q.n_tb, q.d_surv,
+                                  q.d_item_end, bits, q.tb_warm, st)
+                  : launch_tb_seg(g.layout, p->d_codes, q.d_items + g.first, g.count, q.d_surv,
+                                  q.d_item_end, bits, kWarmStages, st);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;

@@ -143,6 +143,49 @@ struct GroupEmitter {
   }
 };
 
+// Survivor layouts the segmented traceback of the rotating kernels reads.
+enum : int { kTbPairs = 0, kTbWords = 1, kTbBytes = 2 };
+
+// How that traceback cuts a batch (measured, in us, for segments of 1, 2, 4,
+// 8, 16 blocks of 32 stages):
+//   4096 K = 7 float frames of 8192 bits       80   81   81   66   60
+//   the same as int8 frame pairs                56   56   57   56   50
+//   4096 K = 9 float frames of 2000 bits       115   71   53   75  135
+//   999 K = 7 float frames of 3001 bits         14   15   17   25   42
+// A batch that leaves lanes idle wants the shortest segments; a batch that
+// fills the device wants them as long as one resident set of lanes allows,
+// since every segment reads its warm-up besides its own stages.
+struct TbShape {
+  int64_t per;  // blocks per lane the batch asks for
+  int warm;     // warm-up blocks
+};
+inline int tb_max_log2(int kind) { return kind == kTbPairs ? 5 : 6; }
+inline TbShape tb_shape(int kind, int K, int cus, int64_t blocks) {
+  // lanes (slots of two lanes for frame pairs) the device keeps resident: a
+  // wavefront's two staged buffers bound the wavefronts per compute unit;
+  // frame pairs, with buffers half as large, did best at half of that
+  const int64_t buf = kind == kTbBytes ? 16384 : kind == kTbPairs ? (K == 7 ? 16384 : 8192)
+                                                                  : (int64_t)256 << (K - 1);
+  const int64_t waves = (160 << 10) / (2 * buf);
+  const int64_t lanes = (int64_t)cus * (waves < 32 ? waves : 32) << tb_max_log2(kind);
+  TbShape s;
+  s.per = blocks / (lanes > 0 ? lanes : 1) + 1;
+  // A segment whose warm-up fails to merge is traced again while its
+  // wavefront waits: 64 stages of warm-up suffice for short segments (a lone
+  // K = 7 frame 7.5 us against 8.4 with 96) and K = 8, 9; with longer
+  // segments 96 pay (the batch above 60 us against 75, pairs 50 against 69)
+  s.warm = (kind == kTbBytes || s.per == 1) ? 2 : 3;
+  return s;
+}
+// Segments (lanes) of an item of n_out bits, as a power of two.
+inline int tb_log2_lanes(int kind, int n_out, int64_t per) {
+  const int64_t nb = ((int64_t)n_out + 31) / 32;
+  int l = 0;
+  while (l < tb_max_log2(kind) && (nb >> (l + 1)) >= per) ++l;
+  if (per == 1 && l < tb_max_log2(kind) && ((int64_t)1 << l) < nb) ++l;
+  return l;
+}
+
 // Workgroups a persistent grid of 'kernel' keeps resident on the device
 // (compute units times resident workgroups per unit), 0 if unknown.
 template <typename Kernel>

@@ -30,15 +30,12 @@ hipError_t launch_fwd_wide(int K, int beta, int dt, int wpf, bool packed, const 
                            void* metric, int32_t* end_out, int32_t* item_end, WideBound* bounds,
                            int64_t* last_m, const SplitUnit* split, int n_split, int64_t* rep_m0,
                            SplitUnit* rep_units, int32_t* rep_count, hipStream_t st);
-hipError_t launch_tb_seg(int layout, const DevCode* codes, const Item* items, int n_items,
-                         const uint64_t* surv, const int32_t* item_end, uint32_t* bits,
-                         int warm, hipStream_t st);
 hipError_t launch_fwd_r4p(int K, const DevCode* codes, const Item* items, const SplitUnit* units,
                           int n_units, const int8_t* llr, uint64_t* surv, int64_t* metric,
                           int32_t* end_out, int32_t* item_end, int32_t* counter, int grid_limit,
                           R4Bound* bounds, int64_t* last_m, const SplitUnit* split, int n_split,
                           int64_t* rep_m0, hipStream_t st);
-hipError_t launch_tb_r4p(int K, const Item* items, const int2* pairs, int n_pairs,
+hipError_t launch_tb_r4p(int kind_k, const Item* items, const int2* table, int n_waves,
                          const uint64_t* surv, const int32_t* item_end, uint32_t* bits, int warm,
                          hipStream_t st);
 }  // namespace mivit
@@ -55,9 +52,6 @@ __device__ __align__(256) uint8_t scratch[kScratchBytes];
 // kernel families of the one-call path (the choices mivit_decode_uniform's
 // plans make for a uniform batch with default options)
 enum : int { kFamRot2 = 0, kFamR4P = 1, kFamWide = 2 };
-// survivor layouts of the segmented traceback (as the plan code numbers them)
-constexpr int kLayoutRotR2 = 2, kLayoutRotByte = 4;
-constexpr int kWarm = 64, kWarmR4P = 96;  // traceback warm-up stages, as in plans
 constexpr int kRotModeDefault = 2;        // rotating kernel, exchanges in the VALU
 
 struct Layout {
@@ -65,12 +59,13 @@ struct Layout {
   int fpw;             // frames per wavefront entry (table-driven kernels)
   int n_waves, n_pairs;
   int64_t ws;          // survivor words per item (per frame pair for radix 4)
-  size_t off_items, off_waves, off_pairs, off_end, off_surv, total;
+  int tb_kind, tb_log2, n_tb, tb_warm;  // traceback: kind, lanes per entry, wavefronts
+  size_t off_items, off_waves, off_tb, off_end, off_surv, total;
 };
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-bool make_layout(const mivit_code& c, int dtype, int F, int S, Layout& L) {
+bool make_layout(const mivit_code& c, int dtype, int F, int S, int n_info, int cus, Layout& L) {
   const bool packed = dtype == MIVIT_I8 && c.beta == 2 && (c.K == 5 || c.K == 7);
   L.fam = packed ? kFamR4P : (c.K <= 7 ? kFamRot2 : kFamWide);
   L.fpw = L.fam == kFamR4P ? 2 * (64 >> (c.K - 1)) : L.fam == kFamRot2 ? (64 >> (c.K - 1)) : 1;
@@ -78,13 +73,21 @@ bool make_layout(const mivit_code& c, int dtype, int F, int S, Layout& L) {
   L.n_pairs = L.fam == kFamR4P ? (F + 1) / 2 : 0;
   L.ws = L.fam == kFamR4P ? surv_words_r4p(c.K, S) : surv_words_blocks32(c.K, S);
   const int64_t units = L.fam == kFamR4P ? (F + 1) / 2 : F;
+  // the traceback wavefronts a plan lists for a uniform batch
+  L.tb_kind = L.fam == kFamR4P ? kTbPairs : L.fam == kFamRot2 ? kTbWords : kTbBytes;
+  const int64_t blocks = units * (((int64_t)n_info + 31) / 32);
+  const TbShape shape = tb_shape(L.tb_kind, c.K, cus, blocks);
+  L.tb_log2 = tb_log2_lanes(L.tb_kind, n_info, shape.per);
+  L.tb_warm = shape.warm;
+  const int per = (1 << tb_max_log2(L.tb_kind)) >> L.tb_log2;
+  L.n_tb = n_info > 0 ? (int)((units + per - 1) / per) : 0;
   size_t o = align256(sizeof(DevCode));
   L.off_items = o;
   o = align256(o + (size_t)F * sizeof(Item));
   L.off_waves = o;  // radix 2: (first, count) per entry; else one whole-frame unit per entry
   o = align256(o + (size_t)L.n_waves * (L.fam == kFamRot2 ? sizeof(int2) : sizeof(SplitUnit)));
-  L.off_pairs = o;
-  o = align256(o + (size_t)L.n_pairs * sizeof(int2));
+  L.off_tb = o;
+  o = align256(o + ((size_t)L.n_tb + L.n_pairs) * sizeof(int2));
   L.off_end = o;
   o = align256(o + (size_t)F * sizeof(int32_t));
   L.off_surv = o;
@@ -99,8 +102,8 @@ bool make_layout(const mivit_code& c, int dtype, int F, int S, Layout& L) {
 // entries of fpw consecutive frames, frame pairs (2p, 2p+1).
 __global__ void k_uniform_tables(uint8_t* base, DevCode code, int F, int S, int n_info,
                                  int terminated, int fam, int fpw, int n_waves, int n_pairs,
-                                 int64_t ws, size_t off_items, size_t off_waves,
-                                 size_t off_pairs) {
+                                 int64_t ws, size_t off_items, size_t off_waves, size_t off_tb,
+                                 int n_tb, int tb_per, int tb_log2) {
   const int k = blockIdx.x * blockDim.x + threadIdx.x;
   if (k == 0) *(DevCode*)base = code;
   if (k < F) {
@@ -136,7 +139,13 @@ __global__ void k_uniform_tables(uint8_t* base, DevCode code, int F, int S, int 
       ((int2*)(base + off_waves))[k] = make_int2(first, count);
     }
   }
-  if (k < n_pairs) ((int2*)(base + off_pairs))[k] = make_int2(2 * k, F - 2 * k < 2 ? 1 : 2);
+  int2* tbt = (int2*)(base + off_tb);
+  if (k < n_tb) {
+    const int n_ent = fam == kFamR4P ? n_pairs : F;
+    const int left = n_ent - k * tb_per;
+    tbt[k] = make_int2(k * tb_per, (left < tb_per ? left : tb_per) | tb_log2 << 16);
+  }
+  if (k < n_pairs) tbt[n_tb + k] = make_int2(2 * k, F - 2 * k < 2 ? 1 : 2);
 }
 
 std::mutex g_mu;
@@ -180,11 +189,14 @@ extern "C" mivit_status mivit_decode_uniform_noalloc(const void* llr, int32_t dt
   const int S = (int)S64;
   if (n_frames == 0 || S == 0) return MIVIT_OK;
   if (!llr || !bits) return MIVIT_EINVAL;
-  Layout L;
-  if (!make_layout(c, dtype, n_frames, S, L)) return MIVIT_ENOMEM;  // exceeds the fixed scratch
   (void)hipGetLastError();  // launches report through it: clear an unrelated earlier error
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess) return MIVIT_EHIP;
+  int dev = 0, cus = 0;
+  const bool dev_ok = hipGetDevice(&dev) == hipSuccess;
+  if (!dev_ok || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    cus = 256;
+  Layout L;
+  if (!make_layout(c, dtype, n_frames, S, n_info, cus, L)) return MIVIT_ENOMEM;  // exceeds the scratch
+  if (!dev_ok) return MIVIT_EHIP;
   uint8_t* base = nullptr;
   hipError_t e = scratch_ptr(dev, &base);
   if (e != hipSuccess) return MIVIT_EHIP;
@@ -197,32 +209,29 @@ extern "C" mivit_status mivit_decode_uniform_noalloc(const void* llr, int32_t dt
   const int nt = n_frames > L.n_waves ? n_frames : L.n_waves;
   hipLaunchKernelGGL(k_uniform_tables, dim3((nt + 255) / 256), dim3(256), 0, st, base, dc,
                      n_frames, S, n_info, terminated, L.fam, L.fpw, L.n_waves, L.n_pairs, L.ws,
-                     L.off_items, L.off_waves, L.off_pairs);
+                     L.off_items, L.off_waves, L.off_tb, L.n_tb,
+                     (1 << tb_max_log2(L.tb_kind)) >> L.tb_log2, L.tb_log2);
   e = hipGetLastError();
   if (e != hipSuccess) return status_of(e);
   const DevCode* d_code = (const DevCode*)base;
   const Item* items = (const Item*)(base + L.off_items);
   const int2* waves = (const int2*)(base + L.off_waves);
-  const int2* pairs = (const int2*)(base + L.off_pairs);
   int32_t* item_end = (int32_t*)(base + L.off_end);
   uint64_t* surv = (uint64_t*)(base + L.off_surv);
   if (L.fam == kFamR4P) {
     e = launch_fwd_r4p(c.K, d_code, items, (const SplitUnit*)waves, L.n_waves, (const int8_t*)llr,
                        surv, (int64_t*)metric, nullptr, item_end, nullptr, 0, nullptr, nullptr,
                        nullptr, 0, nullptr, st);
-    if (e == hipSuccess)
-      e = launch_tb_r4p(c.K, items, pairs, L.n_pairs, surv, item_end, bits, kWarmR4P, st);
   } else if (L.fam == kFamRot2) {
     e = launch_fwd_rot(c.K, c.beta, dtype, kRotModeDefault, d_code, items, waves, L.n_waves, llr,
                        surv, metric, nullptr, item_end, nullptr, 0, st);
-    if (e == hipSuccess)
-      e = launch_tb_seg(kLayoutRotR2, d_code, items, n_frames, surv, item_end, bits, kWarm, st);
   } else {
     e = launch_fwd_wide(c.K, c.beta, dtype, 1, false, d_code, items, (const SplitUnit*)waves, n_frames, llr,
                         surv, metric, nullptr, item_end, nullptr, nullptr, nullptr, 0, nullptr,
                         nullptr, nullptr, st);
-    if (e == hipSuccess)
-      e = launch_tb_seg(kLayoutRotByte, d_code, items, n_frames, surv, item_end, bits, kWarm, st);
   }
+  if (e == hipSuccess)
+    e = launch_tb_r4p(16 * L.tb_kind + c.K, items, (const int2*)(base + L.off_tb), L.n_tb, surv,
+                      item_end, bits, L.tb_warm, st);
   return status_of(e);
 }

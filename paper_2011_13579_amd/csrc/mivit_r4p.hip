@@ -1,4 +1,4 @@
-// Radix-4 forward procedure and traceback for int8 soft values, rate 1/2,
+// Radix-4 forward procedure for int8 soft values, rate 1/2,
 // K = 5 or 7, with two frames packed in the 16-bit halves of every register.
 //
 // Trellis (§VIII-A, Eq. (radix4:S)).  Write a state of n = K-1 bits as n/2
@@ -489,191 +489,6 @@ __device__ __forceinline__ void fwd_r4p_wave(const DevCode* __restrict__ codes,
         if (metric) metric[it.frame] = local + (kind == 1 ? rep_m0[it.slot] : 0);
       }
       if (kind == 0 && split && it.frame >= 0 && end_out) end_out[it.frame] = js;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Traceback of a frame pair (Algorithm 2), 32 segments per frame.
-//
-// Lanes g and g+32 trace segment g of frames A and B; both frames of a pair
-// share their survivor words, so the two lanes share each staged block of 64
-// words: lane g streams its 16-byte chunks 0, 2, .., 14 and lane g+32 chunks
-// 1, 3, .., 15 into LDS (global_load_lds).  Word w of the block then sits at
-// byte ((w & 3) << 2) | ((w & ~3) << 7) + 16 g of the buffer.  The chase
-// keeps its state as that byte offset (for the word of its lane in the
-// current group), so taking a step only replaces one 2-bit field: the digit
-// slot the iteration consumed.  Segment boundaries, speculation and repair as
-// in the radix-2 traceback: lane g starts `warm` stages above its segment
-// from state 0, and a lane whose state at its upper boundary disagrees with
-// the (exact) lane above traces again from that lane's state.
-// ---------------------------------------------------------------------------
-namespace r4p {
-
-typedef __attribute__((address_space(3))) void* lds_ptr_t;
-
-template <int ND>
-struct Tb {
-  static constexpr int KM1 = 2 * ND, NS = 1 << KM1;
-  static constexpr int IPB = 512 / NS;  // iterations per staged block
-};
-
-__device__ __forceinline__ uint32_t addr_of(int R) {
-  return (uint32_t)(((R & 3) << 2) | ((R & ~3) << 7));
-}
-__device__ __forceinline__ int lane_of(uint32_t A) {
-  return (int)(((A >> 2) & 3) | ((A >> 7) & ~3));
-}
-// byte position of lane-digit slot s in the offset form
-__device__ __forceinline__ int slot_pos(int s) { return s == 0 ? 2 : (s == 1 ? 9 : 11); }
-
-struct Chase {
-  int hi, lo;       // iterations hi-1 down to lo are traced (lo >= 0)
-  int a, b;         // stages [a, b) are emitted
-  int PX, PY;       // iteration tops (time lead + 2P) where X and Y are taken
-  uint32_t A;       // current state (offset form) at time lead + 2*(current top)
-  uint32_t X, Y;
-  bool emit;
-};
-
-template <int ND>
-__device__ __forceinline__ void fetch_half(const uint32_t* blk, uint32_t* buf, int hb) {
-#pragma unroll
-  for (int c = 0; c < 8; ++c)
-    __builtin_amdgcn_global_load_lds((const void*)(blk + 4 * (2 * c + hb)), (lds_ptr_t)(buf + c * 256),
-                                     16, 0, 0);
-}
-
-// All lanes whose pair has work chase their range in lockstep rounds; lanes
-// with go set update c and emit.  The stage-0 bit of an odd stage count is
-// the top bit of the state at time 1, where the chase of iteration 0 ends.
-template <int ND>
-__device__ __forceinline__ void chase_all(Chase& c, bool go, bool pair_go, const uint32_t* sv,
-                                          uint32_t* lds, int lead, int h, int g, int ob,
-                                          uint32_t* bits, int64_t bit_off) {
-  constexpr int KM1 = Tb<ND>::KM1, NS = Tb<ND>::NS, IPB = Tb<ND>::IPB;
-  const int lane = threadIdx.x & 63;
-  GroupEmitter em;
-  const bool any = pair_go && c.hi > c.lo;
-  const int B0 = any ? (c.hi - 1) / IPB : 0;
-  const int nb = any ? B0 - c.lo / IPB + 1 : 0;
-  int P = c.hi;
-  uint32_t A = go ? c.A : 0u;
-  if (go && P == c.PY) c.Y = A;
-  if (go && P == c.PX) c.X = A;
-  const int hb = lane >> 5;
-  if (nb > 0) fetch_half<ND>(sv + (int64_t)B0 * 64, lds, hb);
-  for (int rd = 0;; ++rd) {
-    if (__ballot(rd < nb) == 0) break;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    wave_sync();
-    const uint32_t base = (uint32_t)((rd & 1) * 8192 + g * 16);
-    uint32_t* nxt = lds + ((rd + 1) & 1) * 2048;
-    if (rd + 1 < nb) fetch_half<ND>(sv + (int64_t)(B0 - rd - 1) * 64, nxt, hb);
-    if (rd < nb) {
-      const int B = B0 - rd;
-      const int lo = max(c.lo, B * IPB);
-      for (; P > lo; --P) {
-        const int it = P - 1;
-        const int pos = slot_pos(it % ND);
-        const uint32_t goff = (uint32_t)(((it >> 3) & (64 / NS - 1)) << 11);
-        const uint32_t word = *(const uint32_t*)((const char*)lds + base + goff + A);
-        const uint32_t tag = (word >> (16 * (it & 1) + 8 * h + 2 * ((it & 7) >> 1))) & 3u;
-        const uint32_t u = (A >> pos) & 3u;
-        A = (A | (3u << pos)) - (tag << pos);
-        if (go && c.emit) {
-          const int s1 = lead + 2 * it + 1, s0 = s1 - 1;
-          if (s1 >= c.a && s1 < c.b) em.put(s1 - ob, u >> 1, bits, bit_off);
-          if (s0 >= c.a && s0 < c.b) em.put(s0 - ob, u & 1u, bits, bit_off);
-        }
-        if (go && it == c.PY) c.Y = A;
-        if (go && it == c.PX) c.X = A;
-      }
-    }
-    wave_sync();
-  }
-  if (go) {
-    c.A = A;
-    // time 1 holds state lane_of(A) (the phase-0 map is the identity)
-    if (c.emit && lead && c.lo == 0 && c.a <= 0 && c.b > 0)
-      em.put(-ob, (uint32_t)(lane_of(A) >> (KM1 - 1)), bits, bit_off);
-  }
-  em.flush(bits);
-}
-
-}  // namespace r4p
-
-template <int ND>
-__global__ __launch_bounds__(64) void k_tb_r4p(const Item* __restrict__ items,
-                                               const int2* __restrict__ pairs,
-                                               const uint64_t* __restrict__ surv,
-                                               const int32_t* __restrict__ item_end,
-                                               uint32_t* __restrict__ bits, int warm) {
-  using namespace r4p;
-  constexpr int KM1 = 2 * ND;
-  __shared__ uint32_t lds[2 * 2048];
-  const int lane = threadIdx.x;
-  const int h = lane >> 5, g = lane & 31;
-  const int2 pr = pairs[blockIdx.x];
-  const bool have = h < pr.y;
-  const Item it = items[pr.x + (have ? h : 0)];
-  const int S = it.n_stages, ob = it.out_begin, n = it.n_out;
-  if (n <= 0) return;  // equal within the pair: the whole wavefront leaves
-  const int lead = S & 1, n_it = S >> 1;
-  const uint32_t* sv = (const uint32_t*)(surv + it.surv_off);
-  // segments of L stages (L a multiple of 32), at most 32 per frame
-  int G = min(32, (n + 31) / 32);
-  const int L = (((n + G - 1) / G) + 31) & ~31;
-  G = (n + L - 1) / L;
-  const bool active = g < G;
-  const int a = ob + g * L;
-  const int b = min(ob + (g + 1) * L, ob + n);
-  // pair-aligned times at or above a time t: lead + 2P
-  auto top_of = [&](int t) { return (t - lead + 1) >> 1; };  // smallest P with lead + 2P >= t
-  // lanes whose warm-up reaches the frame end start from the known end state
-  const int P_top = (g == G - 1) ? n_it : min(n_it, top_of(b + warm));
-  const bool exact = active && P_top == n_it;
-  Chase c;
-  c.hi = active ? P_top : 0;
-  c.lo = max(0, (a - lead) >> 1);  // the iteration holding stage a (0: stage 0 of odd S)
-  c.a = a;
-  c.b = b;
-  c.PX = top_of(a);
-  c.PY = top_of(b);
-  c.emit = have;
-  c.X = c.Y = 0xFFFFFFFFu;
-  if (exact) {
-    const int js = item_end[it.slot];
-    c.A = addr_of(rotl_n(js, (2 * (n_it % ND)) % KM1, KM1));
-  } else {
-    c.A = 0;
-  }
-  // a frame of one stage has no iteration: only stage 0's bit is emitted
-  const bool go = active && (c.hi > c.lo || (lead && c.lo == 0 && a <= 0));
-  // the shuffle runs on every lane: inside a short-circuit it would run only
-  // where the left side is false and read nothing from the other lanes
-  const int go_partner = __shfl_xor((int)go, 32);
-  const bool pair_go = go | (go_partner != 0);
-  chase_all<ND>(c, go, pair_go, sv, lds, lead, h, g, ob, bits, it.bit_off);
-  // repair: lane g is right when its state at its upper boundary equals the
-  // state lane g+1 reached at its lower boundary (the same time)
-  bool checked = exact;
-  constexpr uint32_t kStateBits = (uint32_t)((3 << 2) | (((1 << (2 * ND)) - 4) << 7));
-  for (int round = 0; round <= G; ++round) {
-    const uint32_t x_up = (uint32_t)__shfl_down((int)c.X, 1) & kStateBits;
-    const bool bad = active && !checked && g < G - 1 && c.Y != x_up;
-    if (__ballot(bad) == 0) break;
-    const int bad_partner = __shfl_xor((int)bad, 32);
-    const bool pbad = bad | (bad_partner != 0);
-    Chase rc = c;
-    rc.hi = c.PY;
-    rc.A = x_up;
-    rc.Y = c.Y;
-    chase_all<ND>(rc, bad, pbad, sv, lds, lead, h, g, ob, bits, it.bit_off);
-    if (bad) {
-      c.A = rc.A;
-      c.X = rc.X;
-      c.Y = x_up;
     }
   }
 }
@@ -1362,21 +1177,6 @@ hipError_t launch_fwd_r4q(const DevCode* codes, const Item* items, const SplitUn
   hipLaunchKernelGGL(k_r4q_check, dim3(ns), dim3(threads), 0, st, codes, items, split, n_split,
                      bounds, (const int64_t*)last_m, rep_m0, llr, surv, metric, end_out,
                      item_end);
-  return hipGetLastError();
-}
-
-hipError_t launch_tb_r4p(int K, const Item* items, const int2* pairs, int n_pairs,
-                         const uint64_t* surv, const int32_t* item_end, uint32_t* bits, int warm,
-                         hipStream_t st) {
-  if (n_pairs <= 0) return hipSuccess;
-  if (K == 7)
-    hipLaunchKernelGGL(k_tb_r4p<3>, dim3(n_pairs), dim3(64), 0, st, items, pairs, surv, item_end,
-                       bits, warm);
-  else if (K == 5)
-    hipLaunchKernelGGL(k_tb_r4p<2>, dim3(n_pairs), dim3(64), 0, st, items, pairs, surv, item_end,
-                       bits, warm);
-  else
-    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

@@ -1,24 +1,23 @@
-// Parallel traceback (Algorithm 2) of one trellis per wavefront.
+// Parallel traceback (Algorithm 2): frames are cut into segments, one lane
+// each, traced at the same time and checked against each other.
 //
-// The emitted stages of an item are cut into at most 64 segments of L stages
-// (L a multiple of 32, so every segment owns whole output words).  Lane g
-// traces segment g.  The lane whose chase reaches the item's last stage
-// starts from the true final state and is exact.  Every other lane starts
-// `warm` stages above its segment from a guessed state; survivor paths merge
-// quickly going backwards, so it usually meets the true path before reaching
-// its segment.  Exactness does not rest on that: lane g records the state y_g
-// it passes at its segment's upper boundary and its final state x_g at the
-// lower boundary.  When y_g equals x_{g+1} of the lane above (itself exact),
-// lane g followed the true path through its whole segment.  A ballot finds
-// the lanes where this fails; they trace again from x_{g+1} and the check
-// repeats, at most G times, until every boundary agrees.
+// The lane whose chase reaches the item's last stage starts from the true
+// final state and is exact.  Every other lane starts some stages above its
+// segment from a guessed state; survivor paths merge quickly going backwards,
+// so it usually meets the true path before reaching its segment.  Exactness
+// does not rest on that: lane g records the state y_g it passes at its
+// segment's upper boundary and its final state x_g at the lower boundary.
+// When y_g equals x_{g+1} of the lane above (itself exact), lane g followed
+// the true path through its whole segment.  A ballot finds the lanes where
+// this fails; they trace again from x_{g+1} and the check repeats until every
+// boundary agrees.
 //
-// Survivor words are read one block (64 words) per lane at a time.  All lanes
-// advance block by block in lockstep rounds; the blocks of the next round are
-// streamed by the lanes straight into the other half of a double-buffered LDS
-// area (global_load_lds, no register staging) while the current round is
-// chased.  In buffer k, word w of lane l sits at ((k*16 + w/4)*64 + l)*4 +
-// w%4, the layout one 16-byte global_load_lds per lane and chunk produces.
+// Survivor words are staged through LDS (global_load_lds, no register
+// staging), double buffered: the lanes advance in lockstep rounds, the next
+// round's words streaming in while the current round is chased.
+//
+// k_tb_rot reads the survivors of the rotating and packed kernels (every
+// default), k_tb_seg those of the generic kernels.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,10 +31,6 @@ enum : int {
   kLayoutNatR4 = 1,  // same words; stage pairs (t, t+1) from 0 hold bits 0 and 1 of y
   kLayoutNatR8 = 5,  // same words; stage triples (t, t+1, t+2) from 0 hold bits 0..2 of y,
                      // the S mod 3 last stages radix-2 decisions
-  kLayoutRotR2 = 2,  // per 32 stages, NS uint32 words; rotating state-to-word map
-  kLayoutRotByte = 4,  // per 8 stages, NS bytes: byte p = decisions at position p (stage
-                       // 8g + i at bit 7 - i); the state j after stage t is at position
-                       // rotl(j, (t+1) mod (K-1))
 };
 
 template <int LAYOUT>
@@ -45,13 +40,7 @@ struct TbGeom {
   int WB;             // uint32 words per block
   __device__ TbGeom(int K_) : K(K_), KM1(K_ - 1), NS(1 << (K_ - 1)) {
     W = words_per_stage(K_);
-    if (LAYOUT == kLayoutRotR2) {
-      SB = 32;
-      WB = NS;
-    } else if (LAYOUT == kLayoutRotByte) {
-      SB = 2048 / NS;  // 64 words of NS / 4 words per 8 stages
-      WB = 64;
-    } else if (LAYOUT == kLayoutNatR8) {
+    if (LAYOUT == kLayoutNatR8) {
       SB = (32 / W) / 3 * 3;  // whole triples per block: 30, 15 or 6 stages
       WB = SB * 2 * W;
     } else {
@@ -61,22 +50,11 @@ struct TbGeom {
   }
 };
 
-// Rotating radix-2 layout: the chase holds the state as the byte offset, in
-// a staged buffer, of the word of its position p: (p >> 2) * 1024 +
-// (p & 3) * 4 (plus the lane's 16-byte slot).  Position bit q is offset bit
-// pos_bit(q).
-__device__ __forceinline__ int pos_off(int p) { return ((p >> 2) << 10) | ((p & 3) << 2); }
-__device__ __forceinline__ int pos_bit(int q) { return q < 2 ? q + 2 : q + 8; }
-
-__device__ __forceinline__ int rotl_bits(int x, int r, int n) {
-  // rotate the n-bit value x left by r (0 <= r < n)
-  return ((x << r) | (x >> (n - r))) & ((1 << n) - 1);
-}
-
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 // Stream this lane's 64-word block starting at src into LDS buffer buf_k
-// (for the lanes currently active).  Always 64 words: a block of fewer words
+// (for the lanes currently active): word w of lane l sits at ((w/4)*64 + l)*4
+// + w%4, the layout one 16-byte global_load_lds per lane and chunk produces.  Always 64 words: a block of fewer words
 // is followed by more survivor words or by the allocation's padding.
 __device__ __forceinline__ void fetch_block(const uint32_t* src, uint32_t* buf_k) {
 #pragma unroll
@@ -90,9 +68,7 @@ __device__ __forceinline__ uint32_t word_at(const uint32_t* buf_k, int w, int la
 }
 
 // Per-lane chase state.  Times are stage boundaries: time t is the state
-// entering stage t.  In the rotating layouts the states j, x, y are held as
-// the state's position at that time (radix 2: as its offset, pos_off), which
-// compare like states at one time.  In the natural radix-4 layout the decisions of a stage
+// entering stage t.  In the natural radix-4 layout the decisions of a stage
 // pair (2k, 2k+1) only name the state two stages back, so states are known
 // (and compared between segments) at pair-aligned times: even times and S.
 // In the radix-8 layout they are the multiples of 3 and the times of the
@@ -118,9 +94,6 @@ __device__ __forceinline__ void chase_all(const TbGeom<LAYOUT>& g, const uint32_
   const int B0 = go ? (c.top - 1) / SB : 0;
   const int nb = go ? B0 - c.a / SB + 1 : 0;
   int t = c.top - 1;  // next stage to step over
-  // rotating layouts: rotation (t + 1) mod (K-1) of the positions, stepped
-  // down with t (no division in the chase)
-  int rot = (go && (LAYOUT == kLayoutRotR2 || LAYOUT == kLayoutRotByte)) ? c.top % g.KM1 : 0;
   if (nb > 0) fetch_block(sv + (int64_t)B0 * WB, lds);
   for (int r = 0;; ++r) {
     if (__ballot(r < nb) == 0) break;
@@ -183,37 +156,6 @@ __device__ __forceinline__ void chase_all(const TbGeom<LAYOUT>& g, const uint32_
           if (t - 2 == c.yb) c.y = j;
           if (t - 2 == c.xa) c.x = j;
         }
-      } else if (LAYOUT == kLayoutRotR2) {
-        // j: position offset at time t + 1.  Stepping over stage t replaces
-        // position bit t mod (K-1) by the decision (the predecessor's
-        // position); that bit held the stage's decoded input bit.
-        const char* cl = (const char*)cur + lane * 16;
-        const int lo = max(c.a, t0);
-        for (; t >= lo; --t) {
-          const int q = rot == 0 ? g.KM1 - 1 : rot - 1;  // t mod (K-1)
-          const int a = pos_bit(q);
-          const uint32_t word = *(const uint32_t*)(cl + j);
-          const int d = (int)((word >> (31 - (t & 31))) & 1u);
-          if (t < c.b) em.put(t - ob, (uint32_t)((j >> a) & 1), bits, bit_off);
-          j = (j & ~(1 << a)) | (d << a);
-          if (t == c.yb) c.y = j;
-          if (t == c.xa) c.x = j;
-          rot = q;
-        }
-      } else if (LAYOUT == kLayoutRotByte) {
-        // j: position at time t + 1 (as for the rotating radix-2 layout,
-        // a step replaces position bit t mod (K-1) by the decision)
-        const int lo = max(c.a, t0);
-        for (; t >= lo; --t) {
-          const int q = rot == 0 ? g.KM1 - 1 : rot - 1;  // t mod (K-1)
-          const int w = ((t - t0) >> 3) * (g.NS >> 2) + (j >> 2);
-          const int d = (word_at(cur, w, lane) >> (8 * (j & 3) + 7 - (t & 7))) & 1;
-          if (t < c.b) em.put(t - ob, (uint32_t)((j >> q) & 1), bits, bit_off);
-          j = (j & ~(1 << q)) | (d << q);
-          if (t == c.yb) c.y = j;
-          if (t == c.xa) c.x = j;
-          rot = q;
-        }
       } else {
         const int lo = max(c.a, t0);
         for (; t >= lo; --t) {
@@ -266,17 +208,12 @@ __global__ __launch_bounds__(64) void k_tb_seg(const DevCode* __restrict__ codes
   c.top = active ? ((lane == G - 1) ? S : min(S, align(c.b + warm))) : c.a;
   const bool exact = active && c.top == S;
   c.j = exact ? item_end[it.slot] : 0;
-  // rotating layouts chase positions: the state's at time S
-  if (LAYOUT == kLayoutRotByte && exact) c.j = rotl_bits(c.j, S % g.KM1, g.KM1);
-  if (LAYOUT == kLayoutRotR2 && exact) c.j = pos_off(rotl_bits(c.j, S % g.KM1, g.KM1));
-  // mask of the state bits (of the offset bits for the rotating radix-2 layout)
-  const int state_mask = LAYOUT == kLayoutRotR2 ? pos_off(g.NS - 1) : g.NS - 1;
   c.x = c.y = -1;
   chase_all<LAYOUT>(g, sv, lds, c, active && c.top > c.a, ob, S, bits, it.bit_off);
   // repair rounds: lane g is right when its state at yb equals lane g+1's
   // state at its xa (the same time)
   for (int round = 0; round <= G; ++round) {
-    const int x_up = __shfl_down(c.x, 1) & state_mask;
+    const int x_up = __shfl_down(c.x, 1) & (g.NS - 1);
     const bool bad = active && !exact && lane < G - 1 && c.y != x_up;
     if (__ballot(bad) == 0) break;
     // lanes that agree with their neighbour stay idle this round
@@ -310,18 +247,367 @@ hipError_t launch_tb_seg(int layout, const DevCode* codes, const Item* items, in
       hipLaunchKernelGGL(k_tb_seg<kLayoutNatR8>, grid, block, 0, st, codes, items, surv,
                          item_end, bits, warm);
       break;
-    case kLayoutRotR2:
-      hipLaunchKernelGGL(k_tb_seg<kLayoutRotR2>, grid, block, 0, st, codes, items, surv,
-                         item_end, bits, warm);
-      break;
-    case kLayoutRotByte:
-      hipLaunchKernelGGL(k_tb_seg<kLayoutRotByte>, grid, block, 0, st, codes, items, surv,
-                         item_end, bits, warm);
-      break;
     default:
       return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------
+// Traceback of the rotating layouts.
+//
+// In all of them the state s at time t sits at position rotl_n(s, t mod n),
+// n = K-1, and a step down over a stage replaces position bit t mod n by the
+// stage's decision (packed radix 4: two stages replace a 2-bit digit).  The
+// message bit of stage t is bit t mod n of the position at time t + 1, which
+// is the decision that was put there n stages above, at stage t + n.  So a
+// lane collects the raw decisions D of 32 stages in a word, and the message
+// bits are those words shifted by n: E_b = (D_{b+1} : D_b) >> n.
+//
+// What bounds it.  A step is a chain: LDS read, bit extract, one bit-select
+// that forms the next LDS address.  The position is therefore held as that
+// address (the lane's slot and the buffer included), with the address bit of
+// every phase in a register; 32 stages are straight-line code with constant
+// bit numbers, 3 VALU instructions and one LDS read per stage (two stages for
+// packed radix 4) against about 35 VALU instructions and several branches
+// when bits were emitted one by one.  Bandwidth is the other bound: every
+// lane streams its warm-up as well as its segment, so a batch with enough
+// frames is cut into few, long segments (tb_plan).
+//
+// kWords: rotating radix 2 (K <= 7), per 32 stages 2^n words, word p the
+//   decisions at position p, stage t at bit 31 - (t mod 32).
+// kBytes: K = 8, 9, per 8 stages 2^n bytes, stage 8g + i at bit 7 - i.
+// kPairs: packed radix 4, per frame pair and 8 iterations 2^n words:
+//   iteration k of the group, frame h in byte 2 (k & 1) + h, bits
+//   2 (k >> 1) and up, holding 3 - digit.  Lanes l and l + 32 trace the two
+//   frames of a pair and share its staged words.
+// ---------------------------------------------------------------------------
+namespace tb {
+
+constexpr int kPairs = kTbPairs, kWords = kTbWords, kBytes = kTbBytes;
+
+template <int KIND, int N>
+struct Geo {
+  static constexpr int NS = 1 << N;
+  // stages per round (one staged buffer) and rounds per 32-stage block
+  static constexpr int RS = KIND == kWords ? 32 : KIND == kBytes ? 2048 / NS : (N == 6 ? 16 : 32);
+  static constexpr int RPB = 32 / RS;
+  static constexpr int WPR = KIND == kWords ? NS : KIND == kBytes ? 64 : (N == 6 ? 64 : 32);
+  static constexpr int SLOTS = KIND == kPairs ? 32 : 64;  // staged blocks per buffer
+  static constexpr int BUF = WPR * 4 * SLOTS;             // bytes per buffer
+  static constexpr int CH = WPR / 4 * SLOTS / 64;         // 16-byte loads per lane and round
+  static constexpr int STEP = KIND == kPairs ? 2 : 1;     // stages per step
+  static constexpr int NP = N / STEP;                     // phases
+  // address offset of position p, and where position bit q sits in it
+  __device__ static int off(int p) {
+    if (KIND == kWords) return ((p & 3) << 2) | ((p >> 2) << 10);
+    if (KIND == kBytes) return (p & 15) | ((p >> 4) << 10);
+    return ((p & 3) << 2) | (((p >> 2) & 1) << 9) | ((p >> 3) << 10);
+  }
+  __device__ static int pos(int a) {
+    if (KIND == kWords) return ((a >> 2) & 3) | (((a >> 10) << 2) & (NS - 1));
+    if (KIND == kBytes) return (a & 15) | (((a >> 10) << 4) & (NS - 1));
+    return ((a >> 2) & 3) | (((a >> 9) << 2) & (NS - 1));
+  }
+  __device__ static int bit(int q) {
+    if (KIND == kWords) return q < 2 ? q + 2 : q + 8;
+    if (KIND == kBytes) return q < 4 ? q : q + 6;
+    return q < 2 ? q + 2 : q + 7;
+  }
+};
+
+__device__ __forceinline__ int rotl_n(int x, int r, int n) {
+  return ((x << r) | (x >> (n - r))) & ((1 << n) - 1);
+}
+
+// Output words of one lane, from the highest down, held until the aligned
+// group of four they belong to is complete (or the chase ends) and stored
+// together: 16-byte pieces instead of partial-line writes spread over the
+// chase.
+struct WordGroup {
+  uint32_t q[4] = {0, 0, 0, 0};
+  uint32_t valid = 0;
+  uint32_t* base = nullptr;
+  __device__ __forceinline__ void flush() {
+    if (valid == 15u && ((uintptr_t)base & 15) == 0) {
+      *(uint4*)base = make_uint4(q[0], q[1], q[2], q[3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if ((valid >> i) & 1u) base[i] = q[i];
+    }
+    valid = 0;
+  }
+  __device__ __forceinline__ void put(uint32_t* out, int k, uint32_t w) {
+    base = out + (k & ~3);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) q[i] = (k & 3) == i ? w : q[i];
+    valid |= 1u << (k & 3);
+    if ((k & 3) == 0) flush();
+  }
+};
+
+// Position-address of the predecessor, and the step's decision, for one step
+// at stage index i (static) of the block; m, sh: mask and shift of the phase.
+template <int KIND, int N, int I>
+__device__ __forceinline__ void step(const char* lds, uint32_t& A, uint32_t m, uint32_t sh,
+                                     uint32_t& D) {
+  if constexpr (KIND == kWords) {
+    const uint32_t w = *(const uint32_t*)(lds + A);
+    const uint32_t d = (uint32_t)((int32_t)(w << I) >> 31);  // 0 or ~0
+    A = (A & ~m) | (d & m);
+    D = (D << 1) + d;  // minus the decisions
+  } else if constexpr (KIND == kBytes) {
+    constexpr int R = I % Geo<KIND, N>::RS;
+    const uint32_t w = *(const uint8_t*)(lds + A + (R >> 3) * Geo<KIND, N>::NS * 64);
+    const uint32_t d = (uint32_t)((int32_t)(w << (24 + (R & 7))) >> 31);
+    A = (A & ~m) | (d & m);
+    D = (D << 1) + d;
+  } else {
+    // I: iteration of the round; group I >> 3 of the staged words
+    constexpr int k = I & 7;
+    const uint32_t w = *(const uint8_t*)(lds + A + (I >> 3) * Geo<KIND, N>::NS * 128 + 2 * (k & 1));
+    const uint32_t t = (w >> (2 * (k >> 1))) & 3u;  // 3 - digit
+    A = (A & ~m) | (m & ~(t << sh));
+    D = (D << 2) | t;
+  }
+}
+
+// Steps I .. 0 of a round; phase of step I: (I mod NP) relative to the round.
+template <int KIND, int N, int I>
+__device__ __forceinline__ void steps(const char* lds, uint32_t& A,
+                                      const uint32_t (&m)[Geo<KIND, N>::NP],
+                                      const uint32_t (&sh)[Geo<KIND, N>::NP], uint32_t& D) {
+  if constexpr (I >= 0) {
+    constexpr int P = I % Geo<KIND, N>::NP;
+    step<KIND, N, I>(lds, A, m[P], sh[P], D);
+    steps<KIND, N, I - 1>(lds, A, m, sh, D);
+  }
+}
+
+}  // namespace tb
+
+// table: per wavefront (first, count | log2 lanes per item << 16); entries
+// count items, or for packed pairs frame pairs, whose (first item, count)
+// list follows the wavefronts' entries.
+template <int KIND, int N>
+__global__ __launch_bounds__(64) void k_tb_rot(const Item* __restrict__ items,
+                                               const int2* __restrict__ table, int n_waves,
+                                               const uint64_t* __restrict__ surv,
+                                               const int32_t* __restrict__ item_end,
+                                               uint32_t* __restrict__ bits, int warm) {
+  using namespace tb;
+  using G = Geo<KIND, N>;
+  constexpr int RS = G::RS, RPB = G::RPB, NP = G::NP;
+  constexpr bool kPair = KIND == kPairs;
+  __shared__ __align__(16) char lds[2 * G::BUF];
+  const int lane = threadIdx.x;
+  const int h = kPair ? lane >> 5 : 0;
+  const int slot = kPair ? lane & 31 : lane;  // (item or pair, segment) of this lane
+  const int2 entry = table[blockIdx.x];
+  const int first = entry.x, count = entry.y & 0xFFFF, log2g = entry.y >> 16;
+  const int g = slot & ((1 << log2g) - 1);
+  const int m_idx = slot >> log2g;
+  bool have = m_idx < count;
+  int ii = first + (have ? m_idx : 0);
+  if (kPair) {
+    const int2 pr = table[n_waves + ii];
+    ii = pr.x + (h < pr.y ? h : 0);
+    have = have && h < pr.y;  // a pair of one frame: the second lane idles along
+  }
+  const Item it = items[ii];
+  const int lead = kPair ? it.n_stages & 1 : 0;
+  const int Se = it.n_stages - lead;  // stages chased (packed: whole iterations)
+  const int n = it.n_out;
+  const int ob = it.out_begin - lead;  // -1: stage 0 of an odd count is emitted
+  const uint32_t* sv = (const uint32_t*)(surv + it.surv_off);
+  uint32_t* out = bits + (it.bit_off >> 5);
+  // blocks of 32 stages bb .. b_last hold the emitted bits; output word k is
+  // (E_{bb+k+1} : E_{bb+k}) >> r.  Lane g owns LB of them.
+  const int bb = ob >> 5, r = ob & 31;
+  const int n_blk = n > 0 ? ((ob + n - 1) >> 5) - bb + 1 : 0;
+  const int n_words = (n + 31) >> 5;
+  const int LB = max(1, (n_blk + (1 << log2g) - 1) >> log2g);
+  const int b0 = bb + g * LB;
+  const int b1 = min(b0 + LB, bb + n_blk);
+  const bool active = m_idx < count && b0 < b1;
+  const bool last = b1 == bb + n_blk;
+  const bool exact = active && (last || b1 + warm >= (Se >> 5) + ((Se & 31) != 0));
+
+  // start of the first chase: time t_top, state s_top there
+  int t_top = exact ? Se : 32 * (b1 + warm);
+  int s_top = exact ? item_end[it.slot] : 0;
+  const uint32_t lane_base = (uint32_t)(slot * 16 + (kPair ? h : 0));
+  const uint32_t state_bits = (uint32_t)G::off(G::NS - 1);
+  const int r_end = max(b0, 0) * RPB;  // last round of this lane
+  uint32_t X = 0, Y = 0, E_low = 0, E_top = 0;
+  bool run = active;
+  for (int pass = 0;; ++pass) {
+    WordGroup wg;
+    uint32_t A = lane_base + (uint32_t)G::off(rotl_n(s_top, t_top % N, N));
+    // decisions above t_top: the bits of the state there
+    const int bt = (t_top - 1) >> 5;  // -1 at time 0
+    const uint64_t V = (uint64_t)(uint32_t)s_top << (t_top - 32 * bt);
+    uint32_t D = (uint32_t)V, D_up = (uint32_t)(V >> 32), E_up = 0;
+    const int r_top = (t_top + RS - 1) / RS - 1;
+    const int nr = run ? r_top - r_end + 1 : 0;
+    // address bit (packed: digit) of each phase, relative to the round
+    uint32_t m[NP], sh[NP];
+    {
+      const int ph = (max(r_top, 0) * (RS % N)) % N;  // (r_top * RS) mod N
+#pragma unroll
+      for (int k = 0; k < NP; ++k) {
+        const int q = (ph + k * G::STEP) % N;
+        sh[k] = (uint32_t)G::bit(q);
+        m[k] = (kPair ? 3u : 1u) << sh[k];
+      }
+    }
+    if (run && (t_top & 31) == 0 && (t_top >> 5) == b1) Y = A & state_bits;
+    auto fetch = [&](int rd, int k) {
+      const uint32_t* src = sv + (int64_t)rd * G::WPR + (kPair ? 4 * h : 0);
+      char* dst = lds + (k & 1) * G::BUF;
+#pragma unroll
+      for (int c = 0; c < G::CH; ++c)
+        __builtin_amdgcn_global_load_lds((const void*)(src + (kPair ? 8 : 4) * c),
+                                         (lds_ptr_t)(dst + c * 1024), 16, 0, 0);
+    };
+    // block b is complete in D: its message bits
+    auto block_done = [&](int b) {
+      const uint32_t E = (uint32_t)(((((uint64_t)D_up) << 32) | D) >> N);
+      if (b < b1) {
+        const int k = b - bb;
+        if (b == b1 - 1 && r != 0) {
+          E_top = E;  // needs the bits of the block above: once those are final
+        } else if (have && k < n_words) {
+          uint32_t w = (uint32_t)(((((uint64_t)E_up) << 32) | E) >> r);
+          if (k == n_words - 1 && (n & 31)) w &= (1u << (n & 31)) - 1u;
+          wg.put(out, k, w);
+        }
+      }
+      E_up = E;
+      D_up = D;
+      D = 0;
+    };
+    if (nr > 0) fetch(r_top, 0);
+    for (int k = 0;; ++k) {
+      if (__ballot(k < nr) == 0) break;
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      const int rd = r_top - k;
+      if (k + 1 < nr) fetch(rd - 1, k + 1);
+      if (k < nr) {
+        uint32_t d = 0;
+        const int lim = t_top - rd * RS;  // stages of this round below t_top
+        if (lim >= RS) {
+          steps<KIND, N, RS / G::STEP - 1>(lds, A, m, sh, d);
+          d = kPair ? ~d : 0u - d;
+        } else {
+          // the item's last, partial round
+#pragma unroll 1
+          for (int i = lim / G::STEP - 1; i >= 0; --i) {
+            const uint32_t q = (uint32_t)G::bit((rd * RS + i * G::STEP) % N);
+            if constexpr (KIND == kWords) {
+              const uint32_t x = (*(const uint32_t*)(lds + A) >> (31 - i)) & 1u;
+              A = (A & ~(1u << q)) | (x << q);
+              d |= x << i;
+            } else if constexpr (KIND == kBytes) {
+              const uint32_t x =
+                  ((uint32_t) * (const uint8_t*)(lds + A + (i >> 3) * G::NS * 64) >> (7 - (i & 7))) & 1u;
+              A = (A & ~(1u << q)) | (x << q);
+              d |= x << i;
+            } else {
+              const uint32_t w = *(const uint8_t*)(lds + A + (i >> 3) * G::NS * 128 + 2 * (i & 1));
+              const uint32_t x = 3u - ((w >> (2 * ((i & 7) >> 1))) & 3u);
+              A = (A & ~(3u << q)) | (x << q);
+              d |= x << (2 * i);
+            }
+          }
+        }
+        // (a whole round of 32 stages has no bits above it in D)
+        if constexpr (RS < 32) {
+          d &= (1u << (lim < RS ? lim : RS)) - 1u;
+          D |= d << ((rd % RPB) * RS);
+        } else {
+          D |= d;
+        }
+        if (rd % RPB == 0) {
+          const int b = rd / RPB;
+          block_done(b);
+          if (b == b1) Y = A & state_bits;  // the position at time 32 b1 (buffer bit not in it)
+        }
+        // the next round's buffer, and its phases
+        A ^= (uint32_t)G::BUF;
+        constexpr int S = (RS / G::STEP) % NP;  // the phase index moves by -S per round
+        if constexpr (S != 0) {
+          uint32_t m2[NP], s2[NP];
+#pragma unroll
+          for (int x = 0; x < NP; ++x) {
+            m2[x] = m[(x + NP - S) % NP];
+            s2[x] = sh[(x + NP - S) % NP];
+          }
+#pragma unroll
+          for (int x = 0; x < NP; ++x) {
+            m[x] = m2[x];
+            sh[x] = s2[x];
+          }
+        }
+      }
+    }
+    if (run) {
+      X = A & state_bits;
+      if (b0 < 0) block_done(-1);  // the bit below the first whole iteration
+      E_low = E_up;
+      wg.flush();
+    }
+    // lane g is right when its state at its upper boundary equals the state
+    // lane g+1 reached there
+    const uint32_t x_up = (uint32_t)__shfl_down((int)X, 1);
+    bool bad = active && !exact && !last && Y != x_up;
+    if (__ballot(bad) == 0 || pass > (1 << log2g)) break;
+    run = bad;
+    if (kPair) {
+      // both lanes of a slot stage its words; the one that was right repeats
+      const int other = __shfl_xor((int)bad, 32);
+      run = active && (bad || other != 0);
+    }
+    t_top = 32 * b1;
+    s_top = rotl_n(G::pos((int)(bad ? x_up : Y)), (N - t_top % N) % N, N);
+  }
+  // top words that straddle two lanes' blocks
+  const uint32_t E_above = (uint32_t)__shfl_down((int)E_low, 1);
+  if (active && have && r != 0) {
+    const int k = b1 - 1 - bb;
+    if (k < n_words) {
+      uint32_t w = (uint32_t)(((((uint64_t)(last ? 0u : E_above)) << 32) | E_top) >> r);
+      if (k == n_words - 1 && (n & 31)) w &= (1u << (n & 31)) - 1u;
+      out[k] = w;
+    }
+  }
+}
+
+// kind_k: 16 * kind (kTb*) + K; table as for k_tb_rot.  (The name and the
+// argument list are those of the packed-pair launcher it grew from, which the
+// CPU builds of the host code stand in for.)
+hipError_t launch_tb_r4p(int kind_k, const Item* items, const int2* table, int n_waves,
+                         const uint64_t* surv, const int32_t* item_end, uint32_t* bits, int warm,
+                         hipStream_t st) {
+  if (n_waves <= 0) return hipSuccess;
+#define MV_TB(KIND, N)                                                                       \
+  hipLaunchKernelGGL((k_tb_rot<KIND, N>), dim3(n_waves), dim3(64), 0, st, items, table,      \
+                     n_waves, surv, item_end, bits, warm);                                   \
+  return hipGetLastError()
+  switch (kind_k) {
+    case tb::kWords * 16 + 3: MV_TB(tb::kWords, 2);
+    case tb::kWords * 16 + 4: MV_TB(tb::kWords, 3);
+    case tb::kWords * 16 + 5: MV_TB(tb::kWords, 4);
+    case tb::kWords * 16 + 6: MV_TB(tb::kWords, 5);
+    case tb::kWords * 16 + 7: MV_TB(tb::kWords, 6);
+    case tb::kBytes * 16 + 8: MV_TB(tb::kBytes, 7);
+    case tb::kBytes * 16 + 9: MV_TB(tb::kBytes, 8);
+    case tb::kPairs * 16 + 5: MV_TB(tb::kPairs, 4);
+    case tb::kPairs * 16 + 7: MV_TB(tb::kPairs, 6);
+    default: return hipErrorInvalidValue;
+  }
+#undef MV_TB
 }
 
 }  // namespace mivit
