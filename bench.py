@@ -42,7 +42,7 @@ COPY_BYTES = 512 << 20
 # forward kernels whose HBM traffic was counted: profile summary and sources
 TRAFFIC_PROFILES = {
     "i8r4": ("fwd_r4q_k7_4096x8192_traffic.md", ["mivit_r4p.hip", "mivit_device.h"]),
-    "f32r2": ("fwd_rot_k7_4096x8192_traffic.md", ["mivit_fwd_rot.hip", "mivit_device.h"]),
+    "f32r2": ("fwd_rot_k7_4096x8192_traffic.md", ["mivit_fwd_rot.h", "mivit_device.h"]),
 }
 # data width of the add-compare-select of each variant's forward kernel
 PACKED16 = {"i8r4"}

@@ -1,0 +1,7 @@
+// Radix-2 forward procedure for K <= 7, exchanges in the vector ALU: float32
+// soft values.
+#include "mivit_fwd_rot.h"
+
+namespace mivit {
+hipError_t launch_rot_f32(MV_ROT_ARGS) { return rot_launch<0, 2>(K, beta, MV_ROT_PASS); }
+}  // namespace mivit
