@@ -30,6 +30,8 @@ namespace mivit {
 
 namespace rot {
 
+constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
+
 __device__ __forceinline__ int parity(uint32_t x) { return __popc(x) & 1; }
 
 __device__ __forceinline__ int branch_out(const DevCode& c, int i, int u) {
@@ -353,8 +355,6 @@ __device__ __forceinline__ void super_block(BlockCtx<KM1, DT, BETA, MODE>& bc, i
   }
 }
 
-constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
-
 }  // namespace rot
 
 // Wavefronts per workgroup: four, one per SIMD, so that every SIMD of a CU
@@ -533,17 +533,19 @@ struct Valu {
   int64_t offset;
   int S, sl, lane;
   uint64_t bad;      // a soft value for slow_blocks was seen
-  // soft values of the block after the next table: of stages row(k)
+  // soft values of the blocks ahead, of stages row(k); block b in lr[b % NB]
   static constexpr int NSTG = LlrRegs<KM1, DT, BETA>::NSTG;
-  T lr[NSTG][BETA];
+  static constexpr int NB0 = KM1 / gcd_c(32, KM1);  // blocks per phase period
+  static constexpr int NB = NB0 == 1 ? 2 : NB0;     // and per trip of the main loop
+  T lr[NB][NSTG][BETA];
   // block stage of register k: every lane has one (64 lanes: each twice)
   __device__ __forceinline__ int row(int k) const { return NS > 32 ? sl & 31 : sl + k * NS; }
-  __device__ __forceinline__ void load(int tb) {
+  __device__ __forceinline__ void load(T (&dst)[NSTG][BETA], int tb) {
 #pragma unroll
     for (int k = 0; k < NSTG; ++k) {
       const int64_t t = min(tb + row(k), S - 1);  // past the end: not used
 #pragma unroll
-      for (int b = 0; b < BETA; ++b) lr[k][b] = (T)llr[t * BETA + b];
+      for (int b = 0; b < BETA; ++b) dst[k][b] = (T)llr[t * BETA + b];
     }
   }
 };
@@ -594,7 +596,8 @@ __device__ __forceinline__ void valu_full(Valu<KM1, DT, BETA>& F) {
 }
 // Table of Eq. (BM) over all output patterns for the soft values in lr.
 template <int KM1, int DT, int BETA>
-__device__ __forceinline__ void valu_table(Valu<KM1, DT, BETA>& F) {
+__device__ __forceinline__ void valu_table(Valu<KM1, DT, BETA>& F,
+                                           const typename Ty<DT>::T (&lr)[Valu<KM1, DT, BETA>::NSTG][BETA]) {
   using T = typename Ty<DT>::T;
   constexpr int NP = 1 << BETA;
 #pragma unroll
@@ -604,7 +607,7 @@ __device__ __forceinline__ void valu_table(Valu<KM1, DT, BETA>& F) {
     for (int p = 0; p < NP / 2; ++p) {
       T v = (T)0;
 #pragma unroll
-      for (int b = 0; b < BETA; ++b) v += ((p >> b) & 1) ? -F.lr[k][b] : F.lr[k][b];
+      for (int b = 0; b < BETA; ++b) v += ((p >> b) & 1) ? -lr[k][b] : lr[k][b];
       row[p] = v;
       row[NP - 1 - p] = -v;
     }
@@ -614,13 +617,14 @@ __device__ __forceinline__ void valu_table(Valu<KM1, DT, BETA>& F) {
 // Note soft values in lr (of any lane) that may bring a NaN or an infinity
 // into the metrics.
 template <int KM1, int DT, int BETA>
-__device__ __forceinline__ void valu_look(Valu<KM1, DT, BETA>& F) {
+__device__ __forceinline__ void valu_look(Valu<KM1, DT, BETA>& F,
+                                          const typename Ty<DT>::T (&lr)[Valu<KM1, DT, BETA>::NSTG][BETA]) {
   if constexpr (!Ty<DT>::kInt) {
     float m = 0.0f;
 #pragma unroll
     for (int k = 0; k < F.NSTG; ++k)
 #pragma unroll
-      for (int b = 0; b < BETA; ++b) m += __builtin_fabsf(F.lr[k][b]);
+      for (int b = 0; b < BETA; ++b) m += __builtin_fabsf(lr[k][b]);
     F.bad |= __builtin_amdgcn_ballot_w64(!(m < 0x1p90f));
   }
 }
@@ -642,14 +646,16 @@ __device__ __forceinline__ void valu_renorm(Valu<KM1, DT, BETA>& F) {
   }
 }
 
-// The next block's table (its metrics' reads follow in program order, and
-// this block's were all issued a block ago) and the soft values after it; tb:
-// this block's first stage.
-template <int KM1, int DT, int BETA>
+// At the start of block BI (of a trip) at stage tb: the next block's table
+// (its metrics' reads follow in program order, and this block's were all
+// issued a block ago) and the soft values a trip after it: a lone wavefront
+// runs 32 stages in less time than memory takes to answer.
+template <int KM1, int DT, int BETA, int BI>
 __device__ __forceinline__ void valu_next(Valu<KM1, DT, BETA>& F, int tb) {
-  valu_look(F);
-  valu_table(F);
-  F.load(tb + 64);
+  auto& lr = F.lr[(BI + 1) % F.NB];
+  valu_look(F, lr);
+  valu_table(F, lr);
+  F.load(lr, tb + 32 * (F.NB + 1));
   wave_sync();
 }
 
@@ -658,7 +664,7 @@ template <int KM1, int DT, int BETA, int BI, int NB>
 __device__ __forceinline__ void valu_period(Valu<KM1, DT, BETA>& F, int t0) {
   if constexpr (BI < NB) {
     const int tb = t0 + 32 * BI;
-    valu_next(F, tb);
+    valu_next<KM1, DT, BETA, BI>(F, tb);
     valu_full<KM1, DT, BETA, (32 * BI) % KM1, 0>(F);
     F.sv[(int64_t)(tb >> 5) << KM1] = F.acc;
     wave_sync();
@@ -672,7 +678,7 @@ template <int KM1, int DT, int BETA, int K, int SUPER>
 __device__ __forceinline__ void valu_tail(Valu<KM1, DT, BETA>& F, int t0, int n) {
   if constexpr (K < SUPER - 1) {
     if (K < n) {
-      if constexpr (K % 32 == 0) valu_next(F, t0 + K);
+      if constexpr (K % 32 == 0) valu_next<KM1, DT, BETA, K / 32>(F, t0 + K);
       valu_stage<KM1, DT, BETA, K % KM1>(F, F.bmv[K % 32]);
       F.bmv[K % 32] = F.tp[(K + 32) % KM1][(K % 32) << BETA];
       if constexpr (K % 32 == 31) {
@@ -720,9 +726,9 @@ template <int KM1, int DT, int BETA>
 __device__ __forceinline__ void slow_blocks(Valu<KM1, DT, BETA>& F, const DevCode& c, int t0) {
 #pragma unroll 1
   for (int tb = t0; tb < F.S; tb += 32) {
-    F.load(tb);
+    F.load(F.lr[0], tb);
     wave_sync();
-    valu_table(F);
+    valu_table(F, F.lr[0]);
     wave_sync();
     const int n = min(32, F.S - tb);
     F.acc = 0;
@@ -748,7 +754,7 @@ __device__ __forceinline__ void fwd_rot_valu_wave(const DevCode* __restrict__ co
   using namespace rot;
   using T = typename Ty<DT>::T;
   constexpr int NS = 1 << KM1;
-  constexpr int SUPER = 32 * KM1 / gcd_c(32, KM1);  // lcm(32, K-1)
+  constexpr int SUPER = 32 * Valu<KM1, DT, BETA>::NB;  // whole phase periods
   const int fr = lane / NS, sl = lane % NS;
   const int2 wv = waves[wave];
   // lanes beyond the entry's frames repeat its first frame (same inputs, same
@@ -779,10 +785,11 @@ __device__ __forceinline__ void fwd_rot_valu_wave(const DevCode* __restrict__ co
                              : q < 4 ? branch_out(c, ie, 0) : branch_out(c, own, 0));
   }
   if (F.S > 0) {
-    F.load(0);
-    valu_look(F);
-    valu_table(F);
-    F.load(32);
+#pragma unroll
+    for (int b = 0; b < F.NB; ++b) F.load(F.lr[b], 32 * b);
+    valu_look(F, F.lr[0]);
+    valu_table(F, F.lr[0]);
+    F.load(F.lr[0], 32 * F.NB);
     wave_sync();
 #pragma unroll
     for (int k = 0; k < 32; ++k) F.bmv[k] = F.tp[k % KM1][k * (1 << BETA)];
