@@ -98,8 +98,10 @@ typedef struct {
   int32_t overlap;  /* stages of overlap on each side of a chunk, >= 0 */
   int32_t variant;  /* kernel variant for tuning and comparison; 0: default
                        (butterfly exchanges through DPP and permlane swaps;
-                       radix 2 with K = 8 or 9: one frame per wavefront with
-                       2^(K-1)/64 states per lane in registers; radix 4
+                       radix 2 with K = 8 or 9: states in registers, int8
+                       with beta <= 3 two to a register in 16-bit metrics,
+                       a float frame over one, two or four wavefronts as
+                       the batch fills the device; radix 4
                        with K = 5 or 7, beta = 2: two frames per register
                        in packed 16-bit metrics; K = 7 batches that fill
                        the device with groups of eight equal-length frames
@@ -128,7 +130,8 @@ typedef struct {
                        serial chain runs with fewer instructions per
                        wavefront; 8: radix 2 with K = 8 or 9, int8, beta
                        <= 3, two states per register in packed 16-bit
-                       metrics (else MIVIT_EUNSUPPORTED) */
+                       metrics (else MIVIT_EUNSUPPORTED; what variant 0
+                       runs there) */
   uint32_t flags;   /* MIVIT_PLAN_* scheduling options, below */
   int32_t reserved[2]; /* must be zero */
 } mivit_opts;

@@ -126,10 +126,6 @@ constexpr int kSplitWavesPerSimdQ = 2;
 constexpr int kWideSplitLen = 1024;
 constexpr int kWideSplitWarm = 192;
 
-// Wavefronts per frame of the K = 8, 9 radix-2 kernel: variants 6 and 7
-// spread a float32 frame's states over two or four wavefronts.
-int waves_per_frame(const Choice& ch) { return ch.variant == 6 ? 2 : ch.variant == 7 ? 4 : 1; }
-
 struct PlanGroup {
   int kern;   // forward kernel
   int layout; // survivor layout (selects the traceback)
@@ -140,6 +136,8 @@ struct PlanGroup {
   int wave_off;  // rotating kernels: first entry of the group in the wave table
   int n_waves;
   int counter;   // persistent launch: index of the group's work counter, else -1
+  int wpf;       // K = 8, 9 kernel: wavefronts per frame (float metrics)
+  bool two16;    // K = 8, 9 kernel: two int8 states per register
 };
 
 struct Part {
@@ -405,6 +403,8 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   g.count = (int)items.size();
   g.wave_off = g.n_waves = 0;
   g.counter = -1;
+  g.wpf = 1;
+  g.two16 = false;
   for (size_t k = 0; k < items.size(); ++k) {
     items[k].slot = (int32_t)k;
     q.total_stages += items[k].n_stages;
@@ -504,14 +504,23 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   if (kern == kKernWide) {
     int64_t total = 0;
     for (const Item& it : items) total += it.n_stages;
-    int slots = 4096;
-    {
-      int dev = 0, cus = 0;
-      if (hipGetDevice(&dev) == hipSuccess &&
-          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-          cus > 0)
-        slots = cus * 4 * kSplitWavesPerSimd;
-    }
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        cus <= 0)
+      cus = 256;
+    const int slots = cus * 4 * kSplitWavesPerSimd;
+    // variants 6 and 7 spread a float frame's states over two or four
+    // wavefronts; variant 0 as the batch wants it.  int8 states go two to a
+    // register wherever the 16-bit form exists (beta <= 3): 4096 K = 9
+    // frames of 2000 bits 440 -> 308 us, one of 1024 74 -> 56, K = 8 218 ->
+    // 173 and 53 -> 42.
+    if (!i8)
+      g.wpf = ch.variant == 6   ? 2
+              : ch.variant == 7 ? 4
+                                : wide_waves(c.K, cus, total, items.empty() ? 0 : items[0].n_stages);
+    else
+      g.two16 = c.beta <= 3;
     const int64_t len = std::max<int64_t>(kWideSplitLen, total / slots);
     const int period = (c.K - 1) == 8 ? 32 : 32 * (c.K - 1);  // lcm(32, K-1) for K = 8, 9
     const int warm = (kWideSplitWarm + period - 1) / period * period;
@@ -641,9 +650,7 @@ hipError_t part_forward(const mivit_plan* p, const Part& q, const void* llr, voi
       e = launch_fwd_r4_mfma(q.mg, p->d_codes, q.d_items + g.first, g.count, (const int8_t*)llr,
                              q.d_surv, (int64_t*)metric, end_state, q.d_item_end, st);
     else if (g.kern == kKernWide)
-      e = launch_fwd_wide(g.K, g.beta, dt, waves_per_frame(q.ch), q.ch.variant == 8,
-                          p->d_codes, q.d_items,
-                          q.d_units, q.n_units, llr, q.d_surv, metric, end_state, q.d_item_end,
+      e = launch_fwd_wide(g.K, g.beta, dt, g.wpf, g.two16, p->d_codes, q.d_items, q.d_units, q.n_units, llr, q.d_surv, metric, end_state, q.d_item_end,
                           q.d_wbounds, q.d_last_m,
                           q.d_split, q.n_split, q.d_rep_m0, q.d_rep_units, q.d_rep_count, st);
     else if (g.kern == kKernRot2)
@@ -726,7 +733,6 @@ std::vector<Choice> candidates(const mivit_code& c, int dtype, int radix) {
       add(2, 1, false);  // LDS exchanges (generic kernel)
       if (dtype == MIVIT_F32) add(2, 6, false);  // registers, two wavefronts per frame
       if (dtype == MIVIT_F32 && c.K == 9) add(2, 7, false);  // four wavefronts per frame
-      if (i8 && c.beta <= 3) add(2, 8, false);  // two states per register, 16-bit
     }
   }
   if (i8 && (radix == 0 || radix == 4)) {
@@ -1138,18 +1144,18 @@ mivit_status mivit_plan_describe(const mivit_plan* p, char* buf, int32_t len) {
     for (const PlanGroup& g : q.groups) {
       // the rotating kernels run a wave table; the others one wavefront per item
       const bool table = g.kern == kKernRot2 || g.kern == kKernRot4P || g.kern == kKernRot4Q;
-      const int wpf = g.kern == kKernWide ? waves_per_frame(q.ch) : 1;
-      const bool two16 = g.kern == kKernWide && q.ch.variant == 8;
       std::snprintf(line, sizeof line,
                     "%scode %d: K=%d beta=%d, %s forward, variant %d, %s, %d items, %d wavefronts",
                     s.empty() ? "" : "; ", q.code, g.K, g.beta, kern_name(g.kern), q.ch.variant,
                     g.counter >= 0 ? "persistent work queue"
                     : table        ? "one wavefront per table entry"
-                    : wpf == 2     ? "two wavefronts per item"
-                    : wpf == 4     ? "four wavefronts per item"
-                    : two16        ? "one wavefront per item, two states per register"
+                    : q.ch.variant == 6 ? "two wavefronts per item"
+                    : q.ch.variant == 7 ? "four wavefronts per item"
+                    : g.wpf == 2   ? "one wavefront per item half"  // of its states
+                    : g.wpf == 4   ? "one wavefront per item quarter"
+                    : g.two16      ? "one wavefront per item, two states per register"
                                    : "one wavefront per item",
-                    g.count, table ? g.n_waves : wpf * g.count);
+                    g.count, table ? g.n_waves : g.wpf * g.count);
       s += line;
     }
   }

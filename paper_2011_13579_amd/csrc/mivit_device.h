@@ -143,6 +143,21 @@ struct GroupEmitter {
   }
 };
 
+// Wavefronts per float frame of the K = 8, 9 kernel, for a part of `stages`
+// stages in all whose longest frame has `longest`.  A lone frame's stages run
+// faster on several wavefronts, a full device wants one each (us, forward
+// pass, K = 9 rate 1/3, 1 / 2 / 4 wavefronts: one frame of 4096 bits
+// 235 / 178 / 175, 256 frames 246 / 186 / 181, 512 251 / 239 / 208, 1024
+// 257 / 253 / 278, 4096 of 2000 bits 344 / 394 / 487; K = 8, 1 / 2
+// wavefronts: 1 frame 130 / 116, 256 139 / 122, 1024 146 / 146): four up to
+// two wavefronts per SIMD, for K = 8 two below that.
+inline int wide_waves(int K, int cus, int64_t stages, int64_t longest) {
+  const int64_t frames = longest > 0 ? (stages + longest - 1) / longest : 0;
+  const int64_t simds = 4 * (int64_t)cus;
+  if (K == 9) return frames * 4 <= 2 * simds ? 4 : 1;
+  return frames * 2 < 2 * simds ? 2 : 1;
+}
+
 // Survivor layouts the segmented traceback of the rotating kernels reads.
 enum : int { kTbPairs = 0, kTbWords = 1, kTbBytes = 2 };
 

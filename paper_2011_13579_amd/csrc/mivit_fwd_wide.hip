@@ -1,259 +1,11 @@
-// Radix-2 forward procedure for K = 8 and 9 (128 and 256 states): one
-// wavefront per frame, R = 2^(K-1)/64 states per lane held in registers.
-//
-// The state-to-position map rotates as in the K <= 7 kernel: at time t the
-// state s sits at position rotl_n(s, t mod n), n = K-1, and position p is
-// register p >> 6 of lane p & 63.  At stage t (phase q = t mod n) both
-// previous states (Eq. (radix2:S): 2f and 2f+1) of the state at position p
-// sit at the positions p with bit q cleared and set, and the new state stays
-// at p.  For q < 6 that is an exchange between lanes, done for each of the R
-// registers: DPP quad permutations fetch both previous metrics for bits 0
-// and 1, v_permlane16/32_swap for bits 4 and 5.  For bits 2 and 3, float
-// metrics stay in the VALU: a lane keeps its own previous state's metric and
-// fetches its partner's (lane ^ 4: row half-mirror then quad reverse; lane ^
-// 8: row rotate by 8); integer metrics fetch both through ds_swizzle, which
-// measured faster for them.  For q >= 6 the two previous states are two
-// registers of the same lane and nothing moves.  The R registers are independent dependency
-// chains, which keeps a lone wavefront busy.
-//
-// Branch metrics: Eq. (BM) for the even previous state on the new state's
-// input; by the corollary of §IV the odd previous state's branch has the
-// opposite value.  A per-wavefront LDS table holds the 2^beta pattern values
-// of each stage of a 32-stage block.
-//
-// Decisions: d = 1 when the odd previous state wins (strict, so a tie keeps
-// the even, lower-index one).  Every position shifts its decision into a
-// 32-bit word; every 32 stages its four bytes go out: per group of 8 stages, 2^(K-1) bytes, byte p
-// holding position p's decisions with stage 8g + i at bit 7 - i.  A group of
-// 8 stages is then 64 (K = 9) or 32 (K = 8) words, the unit the traceback
-// stages through LDS.
-#include <hip/hip_runtime.h>
-#include <stdint.h>
-
-#include "mivit_device.h"
+// Radix-2 forward procedure for K = 8 and 9, int8 soft values: dispatch, the
+// packed 16-bit kernel and the check of frames split in time.  The float
+// kernels are in mivit_fwd_wide_f32.hip and mivit_fwd_wide_f16.hip.
+#include "mivit_fwd_wide.h"
 
 namespace mivit {
 
 namespace wide {
-
-template <int DT>
-struct Ty;
-template <>
-struct Ty<0> {
-  static constexpr bool kInt = false;
-  using T = float;
-  using In = float;
-  __device__ static float unreachable() { return -__builtin_inff(); }
-  __device__ static int bits(float x) { return __builtin_bit_cast(int, x); }
-  __device__ static float from(int x) { return __builtin_bit_cast(float, x); }
-};
-template <>
-struct Ty<1> {
-  static constexpr bool kInt = true;
-  using T = int;
-  using In = int8_t;
-  __device__ static int unreachable() { return -(1 << 29); }
-  __device__ static int bits(int x) { return x; }
-  __device__ static int from(int x) { return x; }
-};
-template <>
-struct Ty<2> : Ty<0> {
-  using In = _Float16;
-};
-
-__device__ __forceinline__ int parity(uint32_t x) { return __popc(x) & 1; }
-
-__device__ __forceinline__ int branch_out(const DevCode& c, int i, int u) {
-  const uint32_t reg = ((uint32_t)u << (c.K - 1)) | (uint32_t)i;
-  int w = 0;
-#pragma unroll
-  for (int b = 0; b < 4; ++b)
-    if (b < c.beta) w |= parity(c.gen[b] & reg) << b;
-  return w;
-}
-
-__device__ __forceinline__ int rotl(int x, int r, int n) {
-  return r == 0 ? x : (((x << r) | (x >> (n - r))) & ((1 << n) - 1));
-}
-__device__ __forceinline__ int rotr(int x, int r, int n) { return rotl(x, (n - r) % n, n); }
-
-// Metrics of the even and odd previous states across lane bit Q (Q < 6).
-template <int Q, int DT>
-__device__ __forceinline__ void pair_fetch(typename Ty<DT>::T x, typename Ty<DT>::T& e,
-                                           typename Ty<DT>::T& o) {
-  const int xi = Ty<DT>::bits(x);
-  int ei, oi;
-  if constexpr (Q == 0) {
-    ei = __builtin_amdgcn_mov_dpp(xi, 0xA0, 0xF, 0xF, true);  // quad_perm [0,0,2,2]
-    oi = __builtin_amdgcn_mov_dpp(xi, 0xF5, 0xF, 0xF, true);  // quad_perm [1,1,3,3]
-  } else if constexpr (Q == 1) {
-    ei = __builtin_amdgcn_mov_dpp(xi, 0x44, 0xF, 0xF, true);  // quad_perm [0,1,0,1]
-    oi = __builtin_amdgcn_mov_dpp(xi, 0xEE, 0xF, 0xF, true);  // quad_perm [2,3,2,3]
-  } else if constexpr (Q <= 3) {
-    // bit-mask mode within 32 lanes: lane' = (lane & and_mask) | or_mask
-    ei = __builtin_amdgcn_ds_swizzle(xi, 0x1F & ~(1 << Q));
-    oi = __builtin_amdgcn_ds_swizzle(xi, 0x1F | ((1 << Q) << 5));
-  } else if constexpr (Q == 4) {
-    // even rows of 16 to every row, odd rows to every row
-    const auto r = __builtin_amdgcn_permlane16_swap(xi, xi, false, false);
-    ei = r[0];
-    oi = r[1];
-  } else {
-    const auto r = __builtin_amdgcn_permlane32_swap(xi, xi, false, false);
-    ei = r[0];
-    oi = r[1];
-  }
-  e = Ty<DT>::from(ei);
-  o = Ty<DT>::from(oi);
-}
-
-// Stages at lane bits 2 and 3 in own/partner form (float metrics).
-template <int DT, int Q>
-constexpr bool own_partner() {
-  return (Q == 2 || Q == 3) && !Ty<DT>::kInt;
-}
-
-// Metric of the partner lane (lane ^ 2^Q) for Q = 2, 3.
-template <int Q, int DT>
-__device__ __forceinline__ typename Ty<DT>::T partner_fetch(typename Ty<DT>::T x) {
-  const int xi = Ty<DT>::bits(x);
-  int pi;
-  if constexpr (Q == 2) {
-    const int hm = __builtin_amdgcn_mov_dpp(xi, 0x141, 0xF, 0xF, true);  // row_half_mirror: ^7
-    pi = __builtin_amdgcn_mov_dpp(hm, 0x1B, 0xF, 0xF, true);            // quad_perm [3,2,1,0]: ^3
-  } else {
-    pi = __builtin_amdgcn_mov_dpp(xi, 0x128, 0xF, 0xF, true);  // row_ror:8
-  }
-  return Ty<DT>::from(pi);
-}
-
-template <int DT, int R>
-struct Wave {
-  using T = typename Ty<DT>::T;
-  T pm[R];           // metric of the state at position 64 (R w + r) + lane
-  uint32_t acc[R];   // decisions of that position in the current block
-  uint32_t pend[R];  // the previous block's decision words, not yet stored
-  // several wavefronts per frame: LDS exchange area of the frame, the
-  // number of wavefronts, this one's index w in the frame, and the exchange
-  // buffer in use
-  T* xch;
-  int nw, fw, xb;
-};
-
-// All wavefronts of a frame at one point, LDS writes before it visible to
-// LDS reads after it.  One wavefront per frame: program order suffices;
-// several (kWorkgroup): the frame is the workgroup, a barrier.
-template <bool kWorkgroup>
-__device__ __forceinline__ void frame_sync() {
-  if constexpr (!kWorkgroup) {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  } else {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-  }
-}
-
-
-// The larger of two metrics: v_max for floats too, so that the select does
-// not wait on the comparison's mask (no NaN arises: finite soft values, and
-// -inf plus finite branch metrics for unreachable float states).
-__device__ __forceinline__ float tmax(float a, float b) { return __builtin_fmaxf(a, b); }
-__device__ __forceinline__ int tmax(int a, int b) { return a > b ? a : b; }
-
-// push_decision for every register of a stage: one wait state pair for all
-// of them (a VALU-written SGPR read as carry needs two).
-template <int R>
-__device__ __forceinline__ void push_decisions(uint32_t (&acc)[R], const uint64_t (&d)[R]) {
-  if constexpr (R == 4) {
-    uint64_t c0, c1, c2, c3;
-    asm("s_nop 1\n\t"
-        "v_addc_co_u32_e64 %0, %4, %0, %0, %8\n\t"
-        "v_addc_co_u32_e64 %1, %5, %1, %1, %9\n\t"
-        "v_addc_co_u32_e64 %2, %6, %2, %2, %10\n\t"
-        "v_addc_co_u32_e64 %3, %7, %3, %3, %11"
-        : "+v"(acc[0]), "+v"(acc[1]), "+v"(acc[2]), "+v"(acc[3]), "=s"(c0), "=s"(c1), "=s"(c2),
-          "=s"(c3)
-        : "s"(d[0]), "s"(d[1]), "s"(d[2]), "s"(d[3]));
-  } else {
-#pragma unroll
-    for (int r = 0; r < R; ++r) acc[r] = push_decision(acc[r], d[r]);
-  }
-}
-
-// One stage at phase Q; bm[r] the branch metric of position 64r + lane: of
-// its even previous state, or in own/partner form of its own previous state
-// (the state at position 64r + lane before the stage).  Own/partner form: the
-// candidates are own + bm and partner - bm in every lane (by the corollary
-// the other previous state's branch has the opposite value); the odd
-// previous state won when partner > own where the lane's bit Q is 0 and
-// own > partner where it is 1, strictly, so a tie keeps the even state.
-template <int KM1, int DT, int R, int Q>
-__device__ __forceinline__ void stage(Wave<DT, R>& W, const typename Ty<DT>::T (&bm)[R]) {
-  using T = typename Ty<DT>::T;
-  T nv[R];
-  uint64_t d[R];  // lanes whose odd previous state won
-  if constexpr (Q >= 6 && (1 << (Q - 6)) >= R) {
-    // bit Q is bit wb of the wavefront index (several per frame): the
-    // wavefronts with that bit clear hold the even previous states, their
-    // partners (index ^ wb) the odd ones, at the same register and lane;
-    // each writes its metrics to the exchange buffer and reads its partner's
-    constexpr int wb = (1 << (Q - 6)) / R;
-    const int lane = threadIdx.x & 63;
-    const int nw = W.nw;
-    T* mine = W.xch + (nw * W.xb + W.fw) * (64 * R);
-    const T* theirs = W.xch + (nw * W.xb + (W.fw ^ wb)) * (64 * R);
-#pragma unroll
-    for (int r = 0; r < R; ++r) mine[64 * r + lane] = W.pm[r];
-    frame_sync<true>();
-    const bool odd = (W.fw & wb) != 0;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const T other = theirs[64 * r + lane];
-      const T e = odd ? other : W.pm[r], o = odd ? W.pm[r] : other;
-      const T ce = e + bm[r], co = o - bm[r];
-      nv[r] = tmax(ce, co);
-      d[r] = __builtin_amdgcn_ballot_w64(co > ce);
-    }
-    // double buffered: the next exchange writes the other buffer, and the
-    // one after it comes after a barrier that follows these reads
-    W.xb ^= 1;
-  } else if constexpr (own_partner<DT, Q>()) {
-    // lanes with bit Q set hold the odd previous state
-    constexpr uint64_t odd = Q == 2 ? 0xF0F0F0F0F0F0F0F0ull : 0xFF00FF00FF00FF00ull;
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const T cp = partner_fetch<Q, DT>(W.pm[r]) - bm[r];
-      const T co = W.pm[r] + bm[r];
-      nv[r] = tmax(cp, co);
-      d[r] = (__builtin_amdgcn_ballot_w64(cp > co) & ~odd) |
-             (__builtin_amdgcn_ballot_w64(co > cp) & odd);
-    }
-  } else if constexpr (Q < 6) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      T e, o;
-      pair_fetch<Q, DT>(W.pm[r], e, o);
-      const T ce = e + bm[r], co = o - bm[r];
-      nv[r] = tmax(ce, co);
-      d[r] = __builtin_amdgcn_ballot_w64(co > ce);
-    }
-  } else {
-    constexpr int rb = 1 << (Q - 6);
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int re = r & ~rb, ro = r | rb;
-      const T ce = W.pm[re] + bm[r], co = W.pm[ro] - bm[r];
-      nv[r] = tmax(ce, co);
-      d[r] = __builtin_amdgcn_ballot_w64(co > ce);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < R; ++r) W.pm[r] = nv[r];
-  push_decisions<R>(W.acc, d);
-}
 
 // Branch metrics are read from LDS kPrefetch stages ahead of their use: a
 // lone wavefront (the longest frame of a batch, once the others are done)
@@ -298,30 +50,6 @@ __device__ __forceinline__ void prefetch_first(typename Ty<DT>::T (&q)[kPrefetch
   }
 }
 
-// A stage whose phase is only known at run time (the last, partial block).
-template <int KM1, int DT, int R, int NP, int Q>
-__device__ __forceinline__ void stage_dyn(Wave<DT, R>& W, const typename Ty<DT>::T* bmrow,
-                                          const int (&pat)[KM1][R], int q) {
-  if constexpr (Q < KM1) {
-    if (q == Q) {
-      typename Ty<DT>::T bm[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) bm[r] = bmrow[pat[Q][r]];
-      stage<KM1, DT, R, Q>(W, bm);
-    } else {
-      stage_dyn<KM1, DT, R, NP, Q + 1>(W, bmrow, pat, q);
-    }
-  }
-}
-
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-constexpr int gcd_c(int a, int b) { return b == 0 ? a : gcd_c(b, a % b); }
-
 struct Ctx {
   int64_t offset;  // integer metrics: total subtracted by renormalisation
   int S, lane;     // S: one past the last stage this unit runs
@@ -329,20 +57,7 @@ struct Ctx {
   int32_t* v_start;  // split part after the first: boundary record to fill at t_store
   int64_t* m_start;
   uint8_t* pend_dst;  // where the pending decision words go, or null
-  int pos0;           // first position held by this wavefront (64 R w)
 };
-
-// Store one block's decision words: four groups of 8 stages, group g of the
-// block being byte 3 - g of the word.
-template <int KM1, int R>
-__device__ __forceinline__ void store_block(uint8_t* dst, const uint32_t (&a)[R]) {
-  constexpr int NS = 1 << KM1;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) dst[g * NS + 64 * r] = (uint8_t)(a[r] >> (24 - 8 * g));
-  }
-}
 
 // One block of up to 32 stages starting at tb; BI its index in the period
 // of the phase pattern.  lv: this lane's soft values of stage tb + lane
@@ -405,7 +120,7 @@ __device__ __forceinline__ void one_block(Wave<DT, R>& W, Ctx& cx, typename Ty<D
   // last block
   cx.pend_dst = nullptr;
   if (tb >= cx.t_store) {
-    cx.pend_dst = (uint8_t*)sv + (int64_t)(tb >> 3) * (1 << KM1) + cx.pos0 + cx.lane;
+    cx.pend_dst = (uint8_t*)sv + (int64_t)(tb >> 3) * (1 << KM1) + cx.lane;
 #pragma unroll
     for (int r = 0; r < R; ++r) W.pend[r] = n == 32 ? W.acc[r] : W.acc[r] << (32 - n);
   }
@@ -428,94 +143,64 @@ __device__ __forceinline__ void super_block(Wave<DT, R>& W, Ctx& cx, typename Ty
   }
 }
 
-constexpr int kWideWaves = 4;  // independent wavefronts (frames) per workgroup
-
 }  // namespace wide
 
-// One wavefront per unit: a whole item (frame or chunk window), or, for
-// int8 soft values, one part of a frame split in time (kind 0), or a repair
+// One wavefront per unit: a whole item (frame or chunk window), or one part
+// of a frame split in time (kind 0), or a repair
 // of one (kind 1, unit count read from the device).  A part after the first
 // runs `warm` stages from all-zero metrics before it_begin and keeps no
 // decisions from them; a part before the last leaves its end metrics in a
 // boundary record, the last part its own metric, which the check completes.
-//
-// WPF = 2 or 4 (float metrics, whole frames only): WPF wavefronts per
-// frame, a workgroup each, wavefront w holding positions 64 (R w + r) +
-// lane with R = 2^(K-1) / (64 WPF); the stages whose phase is a wavefront
-// bit exchange the metrics through LDS, the others run as with one
-// wavefront.  A lone long frame runs its stages with 1/WPF of the
-// instructions per wavefront.
-template <int KM1, int DT, int BETA, int WPF>
+template <int KM1, int BETA>
 __global__ __launch_bounds__(64 * wide::kWideWaves, 3) void k_fwd_wide(
     const DevCode* __restrict__ codes, const Item* __restrict__ items,
     const SplitUnit* __restrict__ units, int n_units, const int32_t* dev_count, int kind,
     WideBound* bounds, int64_t* last_m, const int64_t* rep_m0,
-    const void* __restrict__ llr_v, uint64_t* __restrict__ surv, void* metric,
+    const int8_t* __restrict__ llr_all, uint64_t* __restrict__ surv, int64_t* metric,
     int32_t* end_out, int32_t* item_end) {
   using namespace wide;
-  using T = typename Ty<DT>::T;
-  using In = typename Ty<DT>::In;
-  static_assert(WPF == 1 || ((WPF == 2 || WPF == 4) && !Ty<DT>::kInt && (1 << (KM1 - 6)) >= WPF),
-                "several wavefronts per frame: float metrics, at least one register each");
-  constexpr int R = (1 << (KM1 - 6)) / WPF, NS = 1 << KM1, NP = 1 << BETA;
-  constexpr int FPB = WPF == 1 ? kWideWaves : 1;  // frames per workgroup
+  constexpr int DT = 1;
+  using T = int;
+  constexpr int R = 1 << (KM1 - 6), NS = 1 << KM1, NP = 1 << BETA;
   constexpr int SUPER = 32 * KM1 / gcd_c(32, KM1);  // lcm(32, K-1)
   __shared__ T bmt_all[kWideWaves][32 * NP];
-  __shared__ T xpm_all[FPB][NS];
-  __shared__ T xch_all[WPF > 1 ? 2 * WPF * 64 * R : 1];
-  __shared__ T red_v[WPF];
-  __shared__ int red_s[WPF];
+  __shared__ T xpm_all[kWideWaves][NS];
   const int wid = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
-  const int fw = WPF == 1 ? 0 : wid;  // wavefront within the frame
   if (dev_count) n_units = min(n_units, __builtin_amdgcn_readfirstlane(*dev_count));
-  const int u = WPF == 1 ? blockIdx.x * kWideWaves + wid : blockIdx.x;
-  // every wavefront of a frame leaves together: the barriers are per frame
-  if (u >= n_units) return;
+  const int u = blockIdx.x * kWideWaves + wid;
+  if (u >= n_units) return;  // no workgroup barriers: safe to leave
   const SplitUnit U = units[u];
   const Item it = items[U.first];
   const DevCode c = codes[it.code];
-  const In* llr = (const In*)llr_v + it.llr_off;
+  const int8_t* llr = llr_all + it.llr_off;
   uint64_t* sv = surv + it.surv_off;
   T* bmt = bmt_all[wid];
-  T* xpm = xpm_all[WPF == 1 ? wid : 0];
+  T* xpm = xpm_all[wid];
   const bool first_part = kind == 0 && U.part == 0;
   const bool split = U.n_parts > 1;
   const int s0 = U.it_begin - U.warm;  // a multiple of SUPER: phases start at 0
 
-  // table offset (pattern) of position 64 (R w + r) + lane at each phase: the
-  // even previous state's branch into the state held there after the stage
+  // table offset (pattern) of position 64 r + lane at each phase: the even
+  // previous state's branch into the state held there after the stage
   int pat[KM1][R];
-#pragma unroll
-  for (int q = 0; q < KM1; ++q) {
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      // the new state at position p, and the previous state whose branch
-      // the stage's metric table entry gives: the even one, or in
-      // own/partner form the one at p (odd when bit q of p is set)
-      const int j = rotr(64 * (R * fw + r) + lane, (q + 1) % KM1, KM1);
-      const bool op = (q == 2 || q == 3) && !Ty<DT>::kInt;
-      const int own = op ? ((lane >> q) & 1) : 0;
-      pat[q][r] = branch_out(c, ((j << 1) | own) & (NS - 1), j >> (KM1 - 1));
-    }
-  }
+  patterns<KM1, DT, R>(pat, c, lane, 0);
   Wave<DT, R> W;
-  W.xch = xch_all;
-  W.nw = WPF;
-  W.fw = fw;
+  W.xch = nullptr;
+  W.nw = 1;
+  W.fw = 0;
   W.xb = 0;
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     if (first_part)
-      W.pm[r] = (it.start_known && (R * fw + r != 0 || lane != 0)) ? Ty<DT>::unreachable()
-                                                                   : (T)0;
+      W.pm[r] = (it.start_known && (r != 0 || lane != 0)) ? Ty<DT>::unreachable() : (T)0;
     else if (kind == 0)
       W.pm[r] = (T)0;  // a later part: all-zero metrics (unknown start)
     else
       W.pm[r] = Ty<DT>::from(bounds[U.bnd + U.part - 1].v_end[64 * r + lane]);  // repair
     W.acc[r] = 0;
   }
-  Ctx cx{0, U.it_end, lane, U.it_begin, nullptr, nullptr, nullptr, 64 * R * fw};
+  Ctx cx{0, U.it_end, lane, U.it_begin, nullptr, nullptr, nullptr};
   if (kind == 0 && U.part > 0) {
     cx.v_start = bounds[U.bnd + U.part - 1].v_start;
     cx.m_start = &bounds[U.bnd + U.part - 1].m_start;
@@ -530,7 +215,7 @@ __global__ __launch_bounds__(64 * wide::kWideWaves, 3) void k_fwd_wide(
     super_block<KM1, DT, BETA, 0, SUPER / 32, R>(W, cx, bmt, llr, lv, pat, sv, t0);
   if (cx.pend_dst) store_block<KM1, R>(cx.pend_dst, W.pend);
 
-  if constexpr (Ty<DT>::kInt) {
+  {
     if (kind == 0 && split && U.part < U.n_parts - 1) {
       // the end of a part before the last: range control as at a block
       // start, then the boundary record
@@ -543,62 +228,17 @@ __global__ __launch_bounds__(64 * wide::kWideWaves, 3) void k_fwd_wide(
     }
   }
 
-  // final metrics: position p holds state rotr(p, S mod (K-1)); best state
-  // with ties to the lowest index
   const int S = cx.S;
-  T bv = Ty<DT>::unreachable();
-  int bs = NS;
-#pragma unroll
-  for (int r = 0; r < R; ++r) {
-    const int s = rotr(64 * (R * fw + r) + lane, S % KM1, KM1);
-    xpm[s] = W.pm[r];
-    if (W.pm[r] > bv || (W.pm[r] == bv && s < bs)) {
-      bv = W.pm[r];
-      bs = s;
-    }
-  }
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const T ov = Ty<DT>::from(__shfl_xor(Ty<DT>::bits(bv), o));
-    const int os = __shfl_xor(bs, o);
-    if (ov > bv || (ov == bv && os < bs)) {
-      bv = ov;
-      bs = os;
-    }
-  }
-  if constexpr (WPF > 1) {
-    // the best of the wavefronts' best states, ties to the lower index
-    if (lane == 0) {
-      red_v[fw] = bv;
-      red_s[fw] = bs;
-    }
-    frame_sync<(WPF > 1)>();
-#pragma unroll
-    for (int k = 0; k < WPF; ++k) {
-      const T ov = red_v[k];
-      const int os = red_s[k];
-      if (ov > bv || (ov == bv && os < bs)) {
-        bv = ov;
-        bs = os;
-      }
-    }
-  } else {
-    frame_sync<(WPF > 1)>();
-  }
-  if (lane == 0 && fw == 0) {
-    const int js = it.end_state >= 0 ? it.end_state : bs;
-    const T vj = xpm[js];
+  int js;
+  const T vj = end_state<KM1, DT, R, 1>(W.pm, S, lane, 0, it.end_state, xpm, nullptr, nullptr, js);
+  if (lane == 0) {
     item_end[it.slot] = js;
     if (it.frame >= 0 && end_out) end_out[it.frame] = js;
-    if constexpr (Ty<DT>::kInt) {
-      const int64_t local = (int64_t)vj + cx.offset;
-      if (kind == 0 && split)
-        last_m[it.slot] = local;  // completed by the check
-      else if (it.frame >= 0 && metric)
-        ((int64_t*)metric)[it.frame] = local + (kind == 1 ? rep_m0[it.slot] : 0);
-    } else {
-      if (it.frame >= 0 && metric) ((float*)metric)[it.frame] = vj;
-    }
+    const int64_t local = (int64_t)vj + cx.offset;
+    if (kind == 0 && split)
+      last_m[it.slot] = local;  // completed by the check
+    else if (it.frame >= 0 && metric)
+      metric[it.frame] = local + (kind == 1 ? rep_m0[it.slot] : 0);
   }
 }
 
@@ -1071,6 +711,12 @@ __global__ __launch_bounds__(64 * wide::kWideWaves) void k_wide_check(
 }
 
 hipError_t launch_zero_i32(int32_t* p, int n, hipStream_t st);
+hipError_t launch_wide_f32(int K, int beta, int wpf, const DevCode* codes, const Item* items,
+                           const SplitUnit* units, int n_units, const void* llr, uint64_t* surv,
+                           void* metric, int32_t* end_out, int32_t* item_end, hipStream_t st);
+hipError_t launch_wide_f16(int K, int beta, int wpf, const DevCode* codes, const Item* items,
+                           const SplitUnit* units, int n_units, const void* llr, uint64_t* surv,
+                           void* metric, int32_t* end_out, int32_t* item_end, hipStream_t st);
 
 hipError_t launch_fwd_wide(int K, int beta, int dt, int wpf, bool packed, const DevCode* codes,
                            const Item* items,
@@ -1080,45 +726,32 @@ hipError_t launch_fwd_wide(int K, int beta, int dt, int wpf, bool packed, const 
                            SplitUnit* rep_units, int32_t* rep_count, hipStream_t st) {
   if (n_units <= 0) return hipSuccess;
   if (n_split > 0 && dt != 1) return hipErrorInvalidValue;  // split frames: int8 only
-  if (wpf != 1 && ((wpf != 2 && !(wpf == 4 && K == 9)) || dt != 0)) return hipErrorInvalidValue;
+  if (wpf != 1 && ((wpf != 2 && !(wpf == 4 && K == 9)) || dt == 1)) return hipErrorInvalidValue;
   if (packed && (dt != 1 || wpf != 1 || beta > 3)) return hipErrorInvalidValue;
+  if (dt != 1) {
+    return dt == 0   ? launch_wide_f32(K, beta, wpf, codes, items, units, n_units, llr, surv,
+                                       metric, end_out, item_end, st)
+           : dt == 2 ? launch_wide_f16(K, beta, wpf, codes, items, units, n_units, llr, surv,
+                                       metric, end_out, item_end, st)
+                     : hipErrorInvalidValue;
+  }
   const dim3 block(64 * wide::kWideWaves);
   const dim3 grid((n_units + wide::kWideWaves - 1) / wide::kWideWaves);
-  if (wpf > 1) {  // float32 whole frames: a workgroup of wpf wavefronts per frame
-#define MV_WIDE2(KM1, B, W)                                                                      \
-  hipLaunchKernelGGL((k_fwd_wide<KM1, 0, B, W>), dim3(n_units), dim3(64 * W), 0, st, codes,      \
-                     items, units, n_units, (const int32_t*)nullptr, 0, bounds, last_m,          \
-                     (const int64_t*)nullptr, llr, surv, metric, end_out, item_end);             \
-  return hipGetLastError()
-    switch (K * 64 + beta * 8 + wpf) {
-      case 8 * 64 + 2 * 8 + 2: MV_WIDE2(7, 2, 2);
-      case 8 * 64 + 3 * 8 + 2: MV_WIDE2(7, 3, 2);
-      case 8 * 64 + 4 * 8 + 2: MV_WIDE2(7, 4, 2);
-      case 9 * 64 + 2 * 8 + 2: MV_WIDE2(8, 2, 2);
-      case 9 * 64 + 3 * 8 + 2: MV_WIDE2(8, 3, 2);
-      case 9 * 64 + 4 * 8 + 2: MV_WIDE2(8, 4, 2);
-      case 9 * 64 + 2 * 8 + 4: MV_WIDE2(8, 2, 4);
-      case 9 * 64 + 3 * 8 + 4: MV_WIDE2(8, 3, 4);
-      case 9 * 64 + 4 * 8 + 4: MV_WIDE2(8, 4, 4);
-      default: return hipErrorInvalidValue;
-    }
-#undef MV_WIDE2
-  }
   const dim3 grid_rep((n_split + wide::kWideWaves - 1) / wide::kWideWaves);
   hipError_t e = hipSuccess;
-#define MV_WIDE(KM1, D, B)                                                                       \
+#define MV_WIDE(KM1, B)                                                                          \
   do {                                                                                           \
-    if constexpr (D == 1 && B <= 3) {                                                             \
+    if constexpr (B <= 3) {                                                                       \
       if (packed)                                                                                 \
         hipLaunchKernelGGL((k_fwd_wpk<KM1, B>), grid, block, 0, st, codes, items, units, n_units, \
                            bounds, last_m, (const int8_t*)llr, surv, (int64_t*)metric, end_out,    \
                            item_end);                                                             \
     }                                                                                             \
     if (!packed)                                                                                  \
-      hipLaunchKernelGGL((k_fwd_wide<KM1, D, B, 1>), grid, block, 0, st, codes, items, units,     \
+      hipLaunchKernelGGL((k_fwd_wide<KM1, B>), grid, block, 0, st, codes, items, units,           \
                          n_units, (const int32_t*)nullptr, 0, bounds, last_m,                     \
-                         (const int64_t*)nullptr, llr,                                            \
-                         surv, metric, end_out, item_end);                                        \
+                         (const int64_t*)nullptr, (const int8_t*)llr, surv, (int64_t*)metric,     \
+                         end_out, item_end);                                                      \
     e = hipGetLastError();                                                                        \
     if (e != hipSuccess || n_split <= 0) return e;                                                \
     e = launch_zero_i32(rep_count, 1, st);                                                        \
@@ -1128,32 +761,21 @@ hipError_t launch_fwd_wide(int K, int beta, int dt, int wpf, bool packed, const 
                        rep_count, (int64_t*)metric);                                              \
     e = hipGetLastError();                                                                        \
     if (e != hipSuccess) return e;                                                                \
-    hipLaunchKernelGGL((k_fwd_wide<KM1, D, B, 1>), grid_rep, block, 0, st, codes, items,         \
+    hipLaunchKernelGGL((k_fwd_wide<KM1, B>), grid_rep, block, 0, st, codes, items,               \
                        (const SplitUnit*)rep_units, n_split, (const int32_t*)rep_count, 1, bounds,\
-                       last_m, (const int64_t*)rep_m0, llr, surv, metric, end_out, item_end);     \
+                       last_m, (const int64_t*)rep_m0, (const int8_t*)llr, surv,                  \
+                       (int64_t*)metric, end_out, item_end);                                      \
     return hipGetLastError();                                                                     \
   } while (0)
-#define MV_WIDE_B(KM1, D)             \
-  switch (beta) {                     \
-    case 2: MV_WIDE(KM1, D, 2);       \
-    case 3: MV_WIDE(KM1, D, 3);       \
-    case 4: MV_WIDE(KM1, D, 4);       \
-    default: return hipErrorInvalidValue; \
-  }
-#define MV_WIDE_D(KM1)                \
-  switch (dt) {                       \
-    case 0: MV_WIDE_B(KM1, 0);        \
-    case 1: MV_WIDE_B(KM1, 1);        \
-    case 2: MV_WIDE_B(KM1, 2);        \
-    default: return hipErrorInvalidValue; \
-  }
-  switch (K) {
-    case 8: MV_WIDE_D(7);
-    case 9: MV_WIDE_D(8);
+  switch (K * 8 + beta) {
+    case 8 * 8 + 2: MV_WIDE(7, 2);
+    case 8 * 8 + 3: MV_WIDE(7, 3);
+    case 8 * 8 + 4: MV_WIDE(7, 4);
+    case 9 * 8 + 2: MV_WIDE(8, 2);
+    case 9 * 8 + 3: MV_WIDE(8, 3);
+    case 9 * 8 + 4: MV_WIDE(8, 4);
     default: return hipErrorInvalidValue;
   }
-#undef MV_WIDE_D
-#undef MV_WIDE_B
 #undef MV_WIDE
 }
 

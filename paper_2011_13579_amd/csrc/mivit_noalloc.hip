@@ -226,7 +226,9 @@ extern "C" mivit_status mivit_decode_uniform_noalloc(const void* llr, int32_t dt
     e = launch_fwd_rot(c.K, c.beta, dtype, kRotModeDefault, d_code, items, waves, L.n_waves, llr,
                        surv, metric, nullptr, item_end, nullptr, 0, st);
   } else {
-    e = launch_fwd_wide(c.K, c.beta, dtype, 1, false, d_code, items, (const SplitUnit*)waves, n_frames, llr,
+    e = launch_fwd_wide(c.K, c.beta, dtype,
+                        dtype == MIVIT_I8 ? 1 : wide_waves(c.K, cus, (int64_t)n_frames * S, S),
+                        dtype == MIVIT_I8 && c.beta <= 3, d_code, items, (const SplitUnit*)waves, n_frames, llr,
                         surv, metric, nullptr, item_end, nullptr, nullptr, nullptr, 0, nullptr,
                         nullptr, nullptr, st);
   }
