@@ -252,4 +252,28 @@ __device__ __forceinline__ uint32_t push_decision(uint32_t acc, uint64_t mask) {
   return out;
 }
 
+// Wavefronts of equal work that share a SIMD should end together: the SIMD
+// serves the oldest first, so one of them runs ahead, ends early and leaves
+// the others without anything to fill their waits (two wavefronts of the
+// packed K = 7 kernel ended at 143 and 220 us).  Called at regular points k =
+// 0, 1, 2, .. of the work, this rotates the issue priority among the SIMD's
+// wavefronts so that any two of the first four slots lead equally often.
+__device__ __forceinline__ int wave_slot() {  // hardware wave slot on the SIMD
+  return __builtin_amdgcn_s_getreg((3 << 11) | 4);
+}
+__device__ __forceinline__ void fair_share(int slot, int k) {
+  const int hi = (k + slot) & 1, lo = ((k >> 1) + (slot >> 1)) & 1;
+  if (hi) {
+    if (lo)
+      __builtin_amdgcn_s_setprio(3);
+    else
+      __builtin_amdgcn_s_setprio(2);
+  } else {
+    if (lo)
+      __builtin_amdgcn_s_setprio(1);
+    else
+      __builtin_amdgcn_s_setprio(0);
+  }
+}
+
 }  // namespace mivit
