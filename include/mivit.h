@@ -88,7 +88,9 @@ typedef struct {
 /* Plan options.  Zero-initialised means: choose automatically. */
 typedef struct {
   int32_t dtype;    /* mivit_dtype of every frame's soft values */
-  int32_t radix;    /* 0: choose; 2: radix-2; 4: radix-4 (int8 only);
+  int32_t radix;    /* 0: choose (radix 4 for int8 K = 5, 7 rate-1/2 codes,
+                       unless the frames are few and short; else radix 2);
+                       2: radix-2; 4: radix-4 (int8 only);
                        8: radix-8, three stages per iteration (the
                        radix-2^rho form of §VIII with rho = 3; int8 only,
                        every code K >= 4, variant 0) */
@@ -259,8 +261,8 @@ mivit_status mivit_decode_grad(mivit_plan* plan, const uint32_t* bits, const flo
  *              f*W + k/32, the last word zero-padded.  Never NULL.
  *   metric     device, n_frames values: float32 (float32 and float16 soft
  *              values) or int64 (int8).  May be NULL.
- * Kernels: packed radix 4 for int8 soft values of K = 5 or 7 rate-1/2 codes,
- * radix 2 otherwise; results are those of a plan over the same frames.
+ * Kernels: those of a plan over the same frames with radix 0; results are
+ * that plan's.
  * Asynchronous on 'stream'.  The library keeps a plan (and its survivor
  * memory, 2^(K-1) bits per stage and frame) per (device, stream, code,
  * dtype, n_frames, n_info, terminated), at most 16, releasing the least

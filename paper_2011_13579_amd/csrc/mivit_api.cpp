@@ -99,7 +99,7 @@ constexpr int kMaxGraphs = 8;  // recorded decode graphs kept per plan
 
 // Kernel choice of one part (all frames of one code).
 struct Choice {
-  int radix = 2;
+  int radix = 2;  // 0: open_radix
   int variant = 0;
   bool persistent = false;
   bool split = true;  // packed radix 4: split long frame pairs in time
@@ -354,6 +354,24 @@ bool quad_pays(const std::vector<Item>& items) {
   return waves >= 2 * 4 * (int64_t)cus;
 }
 
+// Radix of a part whose plan leaves it open: int8 K = 5, 7 rate-1/2 codes run
+// packed radix 4, except few frames too short to be split in time, which
+// radix 2 runs faster: its wavefronts hold half as many frames and a shorter
+// chain per stage.  Forward and traceback, K = 7, us, radix 2 / packed: one
+// frame of 1024 bits 25.8 / 30.6, 512 frames 30.0 / 34.9, 1024 34.0 / 37.4,
+// 2048 50.0 / 42.0; one frame of 2048 bits (split in two) 42.0 / 34.1.  The
+// lines are one radix-2 wavefront per SIMD and the shortest split frame.
+int open_radix(const mivit_code& c, int dtype, const std::vector<Item>& items) {
+  if (dtype != MIVIT_I8 || !packed_ok(c)) return 2;
+  int dev = 0, cus = 0, longest = 0;
+  for (const Item& it : items) longest = std::max(longest, it.n_stages);
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+    return 4;
+  const int64_t waves = ((int64_t)items.size() << (c.K - 1)) / 64;
+  return waves <= 4 * (int64_t)cus && longest < 4 * kSplitMinIt ? 2 : 4;
+}
+
 // Build one part: kernel per item, groups, wave and pair tables, survivor
 // memory, device copies.
 mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
@@ -361,10 +379,11 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
                         int code, Part& q) {
   q = Part();
   q.code = code;
-  q.ch = ch;
   std::vector<Item> items;
   expand_items(codes, frames, fidx, o, items);
   const mivit_code& c = codes[code];
+  if (ch.radix == 0) ch.radix = open_radix(c, dtype, items);
+  q.ch = ch;
   const bool i8 = dtype == MIVIT_I8;
   int kern;
   if (ch.radix == 8)
@@ -927,7 +946,10 @@ mivit_status mivit_plan_create(mivit_plan** out, const mivit_code* codes, int32_
     }
     for (int c : order) {
       Choice base;
-      base.radix = o.radix == 0 ? 2 : o.radix;
+      // variants other than 0 and persistent launches are radix 2 unless asked
+      // otherwise
+      base.radix = o.radix == 0 && (o.variant != 0 || (o.flags & MIVIT_PLAN_PERSISTENT)) ? 2
+                                                                                        : o.radix;
       base.variant = o.variant;
       base.persistent = (o.flags & MIVIT_PLAN_PERSISTENT) != 0;
       base.split = (o.flags & MIVIT_PLAN_NO_SPLIT) == 0;
@@ -1205,12 +1227,6 @@ UniformCache& uniform_cache() {
   return *c;
 }
 
-// Radix of the one-call entry points: the packed radix-4 kernel where it
-// applies (int8, K = 5 or 7, beta = 2), radix 2 otherwise.
-int uniform_radix(const mivit_code& code, int dtype) {
-  return (dtype == MIVIT_I8 && packed_ok(code)) ? 4 : 2;
-}
-
 bool same_code(const mivit_code& a, const mivit_code& b) {
   if (a.K != b.K || a.beta != b.beta) return false;
   for (int k = 0; k < a.beta; ++k)
@@ -1268,7 +1284,7 @@ mivit_status mivit_decode_uniform(const void* llr, int32_t dtype, const mivit_co
     mivit_opts o;
     std::memset(&o, 0, sizeof o);
     o.dtype = dtype;
-    o.radix = uniform_radix(*code, dtype);
+    o.radix = 0;  // the plan's choice
     mivit_status s = mivit_plan_create(&plan, code, 1, fr.data(), n_frames, &o);
     if (s != MIVIT_OK) return s;
     if (cache.entries.size() >= kUniformPlans) {
