@@ -393,6 +393,16 @@ def _cached_plan(key, make):
     return p
 
 
+def _covered_outputs(n_words: int, n_frames: int, stages: int, dt: str, device):
+    """Bit words and metrics of frames that leave none of them unwritten (zeroed
+    where there are no stages and nothing runs)."""
+    torch = _torch()
+    new = torch.empty if n_frames > 0 and stages > 0 else torch.zeros
+    return (new(max(n_words, 1), dtype=torch.int32, device=device),
+            new(max(n_frames, 1), dtype=torch.int64 if dt == "i8" else torch.float32,
+                device=device))
+
+
 def _dtype_name(torch, llr):
     names = {torch.float32: "f32", torch.int8: "i8", torch.float16: "f16"}
     if llr.dtype not in names:
@@ -416,11 +426,9 @@ def decode(llr, code, n_info: int, terminated: bool = True, radix: int = 0, stre
     llr = llr.contiguous()
     if llr.numel() < F * S * code.beta or not llr.is_cuda:
         raise ValueError("llr must be a device tensor of at least %d soft values" % (F * S * code.beta))
+    bits, metric = _covered_outputs(F * wpf, F, S, dt, llr.device)
     if radix == 0:
         dtc = {"f32": MIVIT_F32, "i8": MIVIT_I8, "f16": MIVIT_F16}[dt]
-        bits = torch.zeros(max(F * wpf, 1), dtype=torch.int32, device=llr.device)
-        metric = torch.zeros(max(F, 1), dtype=torch.int64 if dt == "i8" else torch.float32,
-                             device=llr.device)
         st = _capi.load().mivit_decode_uniform(_dptr(llr), dtc, ctypes.byref(code.c_struct()),
                                                F, int(n_info), int(bool(terminated)), _dptr(bits),
                                                _dptr(metric), _stream_handle(stream))
@@ -429,7 +437,7 @@ def decode(llr, code, n_info: int, terminated: bool = True, radix: int = 0, stre
     key = ("u", code, F, n_info, terminated, dt, radix, llr.device.index, _stream_handle(stream))
     plan = _cached_plan(key, lambda: Plan([code], uniform_frames(code, F, n_info, terminated),
                                           dt, radix))
-    bits, metric, _ = plan.decode(llr, stream=stream)
+    plan.decode(llr, bits, metric, None, stream=stream)
     return bits[: F * wpf].view(F, wpf), metric[:F]
 
 
@@ -445,7 +453,8 @@ def decode_stream(llr, code, n_info: int, chunk: int = 2048, overlap: int = 64, 
     fr[0] = (0, 0, n_info, 0, n_info, 0, MIVIT_START_KNOWN)
     key = ("s", code, n_info, chunk, overlap, dt, radix, llr.device.index, _stream_handle(stream))
     plan = _cached_plan(key, lambda: Plan([code], fr, dt, radix, chunk, overlap))
-    bits, metric, end = plan.decode(llr.contiguous(), stream=stream)
+    bits, _ = _covered_outputs((n_info + 31) // 32, 1, n_info, dt, llr.device)
+    plan.decode(llr.contiguous(), bits, None, None, stream=stream)
     return bits[: (n_info + 31) // 32]
 
 
@@ -490,14 +499,16 @@ def _make_autograd():
                    _stream_handle(None))
             plan = _cached_plan(key, lambda: Plan([code], uniform_frames(code, F, n_info, terminated),
                                                   "f32", 2))
-            bits, metric, _ = plan.decode(llr.contiguous())
+            wpf = (n_info + 31) // 32
+            S = n_info + (code.K - 1 if terminated else 0)
+            bits, metric = _covered_outputs(F * wpf, F, S, "f32", llr.device)
+            plan.decode(llr.contiguous(), bits, metric, None)
             ctx.plan = plan
             ctx.save_for_backward(bits)
             ctx.shape = llr.shape
-            wpf = (n_info + 31) // 32
             out_bits = bits[: F * wpf].view(F, wpf)
             ctx.mark_non_differentiable(out_bits)
-            return out_bits, metric[:F].clone()
+            return out_bits, metric if F else metric[:0].clone()
 
         @staticmethod
         def backward(ctx, g_bits, g_metric):
