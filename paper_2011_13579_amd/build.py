@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmivit.so")
 SOURCES = ["mivit_kernels.hip", "mivit_fwd_rot.hip", "mivit_fwd_rot_f32.hip",
            "mivit_fwd_rot_i8.hip", "mivit_fwd_rot_f16.hip", "mivit_traceback.hip", "mivit_r4p.hip",
-           "mivit_fwd_wide.hip", "mivit_fwd_wide_f32.hip", "mivit_fwd_wide_f16.hip",
+           "mivit_fwd_wide.hip", "mivit_fwd_wpk.hip", "mivit_fwd_wide_f32.hip", "mivit_fwd_wide_f16.hip",
            "mivit_api.cpp", "mivit_pipe.cpp", "mivit_noalloc.hip",
            "mivit_r4_mfma.hip"]
 ARCH = os.environ.get("MIVIT_OFFLOAD_ARCH", "gfx950")

@@ -79,6 +79,7 @@ enum : int {
   kLayoutRot4P = 3,
   kLayoutRotByte = 4,  // per 8 stages, 2^(K-1) bytes of positions (wide kernel)
   kLayoutNatR8 = 5,
+  kLayoutRotDigit = 6,  // per 8 stages, 2^(K-1) bytes of radix-4 digits (packed K = 8, 9)
 };
 constexpr int kWarmStages = 64;  // speculative traceback warm-up, generic layouts
 
@@ -86,6 +87,7 @@ constexpr int kWarmStages = 64;  // speculative traceback warm-up, generic layou
 int tb_kind(int layout) {
   return layout == kLayoutRotR2 ? kTbWords
          : layout == kLayoutRotByte ? kTbBytes
+         : layout == kLayoutRotDigit ? kTbDigits
          : layout == kLayoutRot4P ? kTbPairs
                                   : -1;
 }
@@ -119,11 +121,16 @@ constexpr int kSplitWavesPerSimd = 4;
 // The four-states-per-lane kernel holds eight frames per wavefront and four
 // independent chains per lane: it targets fewer wavefronts per SIMD.
 constexpr int kSplitWavesPerSimdQ = 2;
-// Time split of the K = 8, 9 radix-2 kernel (int8): a frame is cut into
-// about S / len parts of whole lcm(32, K-1)-stage periods, len being the
-// batch's stages per wavefront slot (at least kWideSplitLen), later parts
-// warming up for at least kWideSplitWarm stages.
+// Time split of the K = 8, 9 kernels (int8): a frame is cut into about S / len
+// parts of whole phase periods, later parts warming up for at least
+// kWideSplitWarm stages.  A part of less than kWideSplitLen stages runs a
+// fifth or more of its time warming up, which pays only while the device is
+// not filled (decode, K = 9, parts of 1024 / 512 stages: 256 frames of 4096
+// bits 89 / 74 us, one 60 / 52, but 512 of 4000 103 / 112).  128 warm-up stages
+// would take 3% less, but at 1.5 dB they often fail to merge and the frame is
+// run again (512 frames of 4000 bits 226 us against 101).
 constexpr int kWideSplitLen = 1024;
+constexpr int kWideSplitMin = 512;
 constexpr int kWideSplitWarm = 192;
 
 struct PlanGroup {
@@ -528,25 +535,31 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         cus <= 0)
       cus = 256;
-    const int slots = cus * 4 * kSplitWavesPerSimd;
+    const int64_t simds = 4 * (int64_t)cus;
     // variants 6 and 7 spread a float frame's states over two or four
     // wavefronts; variant 0 as the batch wants it.  int8 states go two to a
-    // register wherever the 16-bit form exists (beta <= 3): 4096 K = 9
-    // frames of 2000 bits 440 -> 308 us, one of 1024 74 -> 56, K = 8 218 ->
-    // 173 and 53 -> 42.
+    // register wherever the 16-bit form exists (beta <= 3): in 32 bits, 4096
+    // K = 9 frames of 2000 bits took 440 us (now 272), one of 1024 74 (42),
+    // K = 8 218 and 53 (162 and 35).
     if (!i8)
       g.wpf = ch.variant == 6   ? 2
               : ch.variant == 7 ? 4
                                 : wide_waves(c.K, cus, total, items.empty() ? 0 : items[0].n_stages);
     else
       g.two16 = c.beta <= 3;
-    const int64_t len = std::max<int64_t>(kWideSplitLen, total / slots);
-    const int period = (c.K - 1) == 8 ? 32 : 32 * (c.K - 1);  // lcm(32, K-1) for K = 8, 9
+    if (g.two16) g.layout = kLayoutRotDigit;
+    // about four parts per SIMD; shorter ones than kWideSplitLen only where
+    // that leaves fewer than two per SIMD
+    const int64_t len =
+        std::max(total / (4 * simds),
+                 std::clamp<int64_t>(total / (2 * simds), kWideSplitMin, kWideSplitLen));
+    const int period = g.two16 ? wpk_period(c.K - 1)
+                       : c.K == 9 ? 32 : 32 * (c.K - 1);  // lcm(32, K-1) for K = 8, 9
     const int warm = (kWideSplitWarm + period - 1) / period * period;
     const bool can = ch.split && dtype == MIVIT_I8;
     for (int k = 0; k < (int)items.size(); ++k) {
       const int S = items[k].n_stages;
-      int P = can ? (int)std::min<int64_t>(kSplitMaxParts, (S + len - 1) / len) : 1;
+      int P = can ? (int)std::clamp<int64_t>(S / len, 1, kSplitMaxParts) : 1;
       if (S < 2 * period + warm) P = 1;
       SplitUnit u;
       u.first = k;
@@ -555,7 +568,9 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
       u.bnd = P > 1 ? (int)wbounds.size() : -1;
       int prev = 0;
       for (int p = 0; p < P; ++p) {
-        const int end = p == P - 1 ? S : (int)((int64_t)S * (p + 1) / P) / period * period;
+        // (part 0 has no warm-up: it takes that many stages more)
+        const int64_t T = ((int64_t)S + (int64_t)(P - 1) * warm) / P;
+        const int end = p == P - 1 ? S : (int)(T + p * (T - warm)) / period * period;
         u.part = p;
         u.it_begin = prev;
         u.it_end = end;

@@ -143,6 +143,10 @@ struct GroupEmitter {
   }
 };
 
+// Stages in a trip of the packed K = 8, 9 kernel (n = K - 1): parts of items
+// split in time begin at multiples of it.
+__host__ __device__ constexpr int wpk_period(int n) { return n == 8 ? 64 : 112; }
+
 // Wavefronts per float frame of the K = 8, 9 kernel, for a part of `stages`
 // stages in all whose longest frame has `longest`.  A lone frame's stages run
 // faster on several wavefronts, a full device wants one each (us, forward
@@ -159,7 +163,7 @@ inline int wide_waves(int K, int cus, int64_t stages, int64_t longest) {
 }
 
 // Survivor layouts the segmented traceback of the rotating kernels reads.
-enum : int { kTbPairs = 0, kTbWords = 1, kTbBytes = 2 };
+enum : int { kTbPairs = 0, kTbWords = 1, kTbBytes = 2, kTbDigits = 3 };
 
 // How that traceback cuts a batch (measured, in us, for segments of 1, 2, 4,
 // 8, 16 blocks of 32 stages):
@@ -179,7 +183,7 @@ inline TbShape tb_shape(int kind, int K, int cus, int64_t blocks) {
   // lanes (slots of two lanes for frame pairs) the device keeps resident: a
   // wavefront's two staged buffers bound the wavefronts per compute unit;
   // frame pairs, with buffers half as large, did best at half of that
-  const int64_t buf = kind == kTbBytes ? 16384 : kind == kTbPairs ? (K == 7 ? 16384 : 8192)
+  const int64_t buf = kind >= kTbBytes ? 16384 : kind == kTbPairs ? (K == 7 ? 16384 : 8192)
                                                                   : (int64_t)256 << (K - 1);
   const int64_t waves = (160 << 10) / (2 * buf);
   const int64_t lanes = (int64_t)cus * (waves < 32 ? waves : 32) << tb_max_log2(kind);
@@ -189,7 +193,7 @@ inline TbShape tb_shape(int kind, int K, int cus, int64_t blocks) {
   // wavefront waits: 64 stages of warm-up suffice for short segments (a lone
   // K = 7 frame 7.5 us against 8.4 with 96) and K = 8, 9; with longer
   // segments 96 pay (the batch above 60 us against 75, pairs 50 against 69)
-  s.warm = (kind == kTbBytes || s.per == 1) ? 2 : 3;
+  s.warm = (kind >= kTbBytes || s.per == 1) ? 2 : 3;
   return s;
 }
 // Segments (lanes) of an item of n_out bits, as a power of two.
@@ -222,7 +226,7 @@ __host__ __device__ inline int words_per_stage(int K) {
 
 // Survivor memory of one work item, in uint64 words, per survivor layout
 // (rounded up to an even count so every item starts 16-byte aligned):
-//   rotating radix 2 (K <= 7) and bytes-by-position (K = 8, 9): whole
+//   rotating radix 2 (K <= 7), bytes by position and digits (K = 8, 9): whole
 //     32-stage blocks of 2^(K-1) 32-bit words;
 //   packed radix 4 (one frame pair): 2^(K-1) 32-bit words per 8 iterations;
 //   natural layouts: words_per_stage(K) per stage.

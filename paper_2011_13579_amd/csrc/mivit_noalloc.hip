@@ -74,7 +74,9 @@ bool make_layout(const mivit_code& c, int dtype, int F, int S, int n_info, int c
   L.ws = L.fam == kFamR4P ? surv_words_r4p(c.K, S) : surv_words_blocks32(c.K, S);
   const int64_t units = L.fam == kFamR4P ? (F + 1) / 2 : F;
   // the traceback wavefronts a plan lists for a uniform batch
-  L.tb_kind = L.fam == kFamR4P ? kTbPairs : L.fam == kFamRot2 ? kTbWords : kTbBytes;
+  L.tb_kind = L.fam == kFamR4P ? kTbPairs : L.fam == kFamRot2 ? kTbWords
+              : dtype == MIVIT_I8 && c.beta <= 3 ? kTbDigits
+                                                 : kTbBytes;
   const int64_t blocks = units * (((int64_t)n_info + 31) / 32);
   const TbShape shape = tb_shape(L.tb_kind, c.K, cus, blocks);
   L.tb_log2 = tb_log2_lanes(L.tb_kind, n_info, shape.per);

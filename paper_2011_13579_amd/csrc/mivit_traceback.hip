@@ -277,6 +277,9 @@ hipError_t launch_tb_seg(int layout, const DevCode* codes, const Item* items, in
 // kWords: rotating radix 2 (K <= 7), per 32 stages 2^n words, word p the
 //   decisions at position p, stage t at bit 31 - (t mod 32).
 // kBytes: K = 8, 9, per 8 stages 2^n bytes, stage 8g + i at bit 7 - i.
+// kDigits: packed K = 8, 9, per 8 stages 2^n bytes, position p at byte
+//   (p mod 64) 2^(n-6) + (p >> 6), the radix-4 digit of iteration i in bits
+//   6 - 2i and up.
 // kPairs: packed radix 4, per frame pair and 8 iterations 2^n words:
 //   iteration k of the group, frame h in byte 2 (k & 1) + h, bits
 //   2 (k >> 1) and up, holding 3 - digit.  Lanes l and l + 32 trace the two
@@ -284,34 +287,47 @@ hipError_t launch_tb_seg(int layout, const DevCode* codes, const Item* items, in
 // ---------------------------------------------------------------------------
 namespace tb {
 
-constexpr int kPairs = kTbPairs, kWords = kTbWords, kBytes = kTbBytes;
+constexpr int kPairs = kTbPairs, kWords = kTbWords, kBytes = kTbBytes, kDigits = kTbDigits;
 
 template <int KIND, int N>
 struct Geo {
   static constexpr int NS = 1 << N;
   // stages per round (one staged buffer) and rounds per 32-stage block
-  static constexpr int RS = KIND == kWords ? 32 : KIND == kBytes ? 2048 / NS : (N == 6 ? 16 : 32);
+  static constexpr int RS = KIND == kWords ? 32 : KIND >= kBytes ? 2048 / NS : (N == 6 ? 16 : 32);
   static constexpr int RPB = 32 / RS;
-  static constexpr int WPR = KIND == kWords ? NS : KIND == kBytes ? 64 : (N == 6 ? 64 : 32);
+  static constexpr int WPR = KIND == kWords ? NS : KIND >= kBytes ? 64 : (N == 6 ? 64 : 32);
   static constexpr int SLOTS = KIND == kPairs ? 32 : 64;  // staged blocks per buffer
   static constexpr int BUF = WPR * 4 * SLOTS;             // bytes per buffer
   static constexpr int CH = WPR / 4 * SLOTS / 64;         // 16-byte loads per lane and round
-  static constexpr int STEP = KIND == kPairs ? 2 : 1;     // stages per step
-  static constexpr int NP = N / STEP;                     // phases
+  static constexpr int STEP = KIND == kPairs || KIND == kDigits ? 2 : 1;  // stages per step
+  static constexpr int NP = N % STEP ? N : N / STEP;                      // phases
+  static constexpr int NR = N - 6;  // kDigits: position bits below the lane's
   // address offset of position p, and where position bit q sits in it
   __device__ static int off(int p) {
     if (KIND == kWords) return ((p & 3) << 2) | ((p >> 2) << 10);
     if (KIND == kBytes) return (p & 15) | ((p >> 4) << 10);
+    if (KIND == kDigits) {
+      const int b = ((p & 63) << NR) | (p >> 6);
+      return (b & 15) | ((b >> 4) << 10);
+    }
     return ((p & 3) << 2) | (((p >> 2) & 1) << 9) | ((p >> 3) << 10);
   }
   __device__ static int pos(int a) {
     if (KIND == kWords) return ((a >> 2) & 3) | (((a >> 10) << 2) & (NS - 1));
     if (KIND == kBytes) return (a & 15) | (((a >> 10) << 4) & (NS - 1));
+    if (KIND == kDigits) {
+      const int b = (a & 15) | (((a >> 10) << 4) & (NS - 1));
+      return (b >> NR) | ((b & ((1 << NR) - 1)) << 6);
+    }
     return ((a >> 2) & 3) | (((a >> 9) << 2) & (NS - 1));
   }
   __device__ static int bit(int q) {
     if (KIND == kWords) return q < 2 ? q + 2 : q + 8;
     if (KIND == kBytes) return q < 4 ? q : q + 6;
+    if (KIND == kDigits) {
+      const int b = q < 6 ? q + NR : q - 6;
+      return b < 4 ? b : b + 6;
+    }
     return q < 2 ? q + 2 : q + 7;
   }
 };
@@ -348,7 +364,8 @@ struct WordGroup {
 };
 
 // Position-address of the predecessor, and the step's decision, for one step
-// at stage index i (static) of the block; m, sh: mask and shift of the phase.
+// at stage index i (static) of the block; m, sh: mask and shift of the phase
+// (kDigits: the masks of the digit's two bits).
 template <int KIND, int N, int I>
 __device__ __forceinline__ void step(const char* lds, uint32_t& A, uint32_t m, uint32_t sh,
                                      uint32_t& D) {
@@ -363,6 +380,15 @@ __device__ __forceinline__ void step(const char* lds, uint32_t& A, uint32_t m, u
     const uint32_t d = (uint32_t)((int32_t)(w << (24 + (R & 7))) >> 31);
     A = (A & ~m) | (d & m);
     D = (D << 1) + d;
+  } else if constexpr (KIND == kDigits) {
+    // I: iteration of the round; byte I >> 2 of the position
+    constexpr int b = 6 - 2 * (I & 3);
+    const uint32_t w = *(const uint8_t*)(lds + A + (I >> 2) * Geo<KIND, N>::NS * 64);
+    const uint32_t d0 = (uint32_t)((int32_t)(w << (31 - b)) >> 31);
+    const uint32_t d1 = (uint32_t)((int32_t)(w << (30 - b)) >> 31);
+    A = (A & ~m) | (d0 & m);
+    A = (A & ~sh) | (d1 & sh);
+    D = (D << 2) | ((w >> b) & 3u);
   } else {
     // I: iteration of the round; group I >> 3 of the staged words
     constexpr int k = I & 7;
@@ -416,8 +442,8 @@ __global__ __launch_bounds__(64) void k_tb_rot(const Item* __restrict__ items,
     have = have && h < pr.y;  // a pair of one frame: the second lane idles along
   }
   const Item it = items[ii];
-  const int lead = kPair ? it.n_stages & 1 : 0;
-  const int Se = it.n_stages - lead;  // stages chased (packed: whole iterations)
+  const int lead = G::STEP == 2 ? it.n_stages & 1 : 0;
+  const int Se = it.n_stages - lead;  // stages chased (radix 4: whole iterations)
   const int n = it.n_out;
   const int ob = it.out_begin - lead;  // -1: stage 0 of an odd count is emitted
   const uint32_t* sv = (const uint32_t*)(surv + it.surv_off);
@@ -460,6 +486,7 @@ __global__ __launch_bounds__(64) void k_tb_rot(const Item* __restrict__ items,
         const int q = (ph + k * G::STEP) % N;
         sh[k] = (uint32_t)G::bit(q);
         m[k] = (kPair ? 3u : 1u) << sh[k];
+        if (KIND == kDigits) sh[k] = 1u << G::bit((q + 1) % N);
       }
     }
     if (run && (t_top & 31) == 0 && (t_top >> 5) == b1) Y = A & state_bits;
@@ -499,7 +526,7 @@ __global__ __launch_bounds__(64) void k_tb_rot(const Item* __restrict__ items,
         const int lim = t_top - rd * RS;  // stages of this round below t_top
         if (lim >= RS) {
           steps<KIND, N, RS / G::STEP - 1>(lds, A, m, sh, d);
-          d = kPair ? ~d : 0u - d;
+          d = kPair ? ~d : KIND == kDigits ? d : 0u - d;
         } else {
           // the item's last, partial round
 #pragma unroll 1
@@ -514,6 +541,12 @@ __global__ __launch_bounds__(64) void k_tb_rot(const Item* __restrict__ items,
                   ((uint32_t) * (const uint8_t*)(lds + A + (i >> 3) * G::NS * 64) >> (7 - (i & 7))) & 1u;
               A = (A & ~(1u << q)) | (x << q);
               d |= x << i;
+            } else if constexpr (KIND == kDigits) {
+              const uint32_t q1 = (uint32_t)G::bit((rd * RS + i * 2 + 1) % N);
+              const uint32_t x =
+                  ((uint32_t) * (const uint8_t*)(lds + A + (i >> 2) * G::NS * 64) >> (6 - 2 * (i & 3))) & 3u;
+              A = (A & ~(1u << q) & ~(1u << q1)) | ((x & 1) << q) | ((x >> 1) << q1);
+              d |= x << (2 * i);
             } else {
               const uint32_t w = *(const uint8_t*)(lds + A + (i >> 3) * G::NS * 128 + 2 * (i & 1));
               const uint32_t x = 3u - ((w >> (2 * ((i & 7) >> 1))) & 3u);
@@ -603,6 +636,8 @@ hipError_t launch_tb_r4p(int kind_k, const Item* items, const int2* table, int n
     case tb::kWords * 16 + 7: MV_TB(tb::kWords, 6);
     case tb::kBytes * 16 + 8: MV_TB(tb::kBytes, 7);
     case tb::kBytes * 16 + 9: MV_TB(tb::kBytes, 8);
+    case tb::kDigits * 16 + 8: MV_TB(tb::kDigits, 7);
+    case tb::kDigits * 16 + 9: MV_TB(tb::kDigits, 8);
     case tb::kPairs * 16 + 5: MV_TB(tb::kPairs, 4);
     case tb::kPairs * 16 + 7: MV_TB(tb::kPairs, 6);
     default: return hipErrorInvalidValue;

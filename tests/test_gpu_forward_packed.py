@@ -100,3 +100,15 @@ def test_split_and_whole_agree_on_noise(code, variant):
     x = [rng.integers(-128, 128, 2 * 4001) for _ in range(11)]
     for split in (True, False):
         _check(code, [4001] * 11, [k % 4 for k in range(11)], lambda k, S: x[k], variant, split)
+
+
+@pytest.mark.parametrize("variant", [4, 5])
+def test_boundaries_that_never_merge(variant):
+    """Chains of two states keep the metric difference they start with under
+    soft values of constant size: no warm-up finds it, every boundary is
+    repaired."""
+    rng = np.random.default_rng(variant)
+    S = 6001
+    x = [np.full(2 * S, 100), np.repeat(rng.choice([-90, 90], S), 2),
+         np.repeat(rng.choice([-128, 127], S), 2)]
+    _check(CODE_K7_WIDE, [S] * 3, [1, 3, 1], lambda k, n: x[k], variant)
