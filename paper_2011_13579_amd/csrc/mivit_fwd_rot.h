@@ -795,10 +795,14 @@ __device__ __forceinline__ void fwd_rot_valu_wave(const DevCode* __restrict__ co
     for (int k = 0; k < 32; ++k) F.bmv[k] = F.tp[k % KM1][k * (1 << BETA)];
     int t0 = 0;
     T pm0 = F.pm;  // metrics entering the period from t0
+    // Only where wavefronts share SIMDs, and for float32: 4096 frames of 8198
+    // stages, decode, 416 -> 408 us; float16 took 376 against 369 with it.
+    const int slot = DT == 0 && gridDim.x > 256 ? wave_slot() : -1;
     for (; t0 + SUPER <= F.S && F.bad == 0; t0 += SUPER) {
       pm0 = F.pm;
       valu_period<KM1, DT, BETA, 0, SUPER / 32>(F, t0);
       valu_renorm(F);
+      if (slot >= 0) fair_share(slot, t0 / SUPER);
     }
     if (F.bad != 0) {
       t0 = max(t0 - SUPER, 0);
