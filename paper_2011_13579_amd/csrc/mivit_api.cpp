@@ -116,6 +116,11 @@ struct Choice {
 constexpr int kSplitAlign = 48;
 constexpr int kSplitWarm = 96;
 constexpr int kSplitMinIt = 384;
+// where whole frames leave the device mostly idle, parts may be this short
+// (decode, parts of at least 384 / 144 iterations: 128 windows of 2176 stages
+// 42 / 31 us, 16 frames of 1001 bits 35 / 25, 256 of 2048 38 / 29, 512 of 4096
+// 56 / 51)
+constexpr int kSplitMinItFew = 144;
 constexpr int kSplitMaxParts = kMaxSplitParts;
 constexpr int kSplitWavesPerSimd = 4;
 // The four-states-per-lane kernel holds eight frames per wavefront and four
@@ -365,9 +370,11 @@ bool quad_pays(const std::vector<Item>& items) {
 // packed radix 4, except few frames too short to be split in time, which
 // radix 2 runs faster: its wavefronts hold half as many frames and a shorter
 // chain per stage.  Forward and traceback, K = 7, us, radix 2 / packed: one
-// frame of 1024 bits 25.8 / 30.6, 512 frames 30.0 / 34.9, 1024 34.0 / 37.4,
-// 2048 50.0 / 42.0; one frame of 2048 bits (split in two) 42.0 / 34.1.  The
-// lines are one radix-2 wavefront per SIMD and the shortest split frame.
+// frame of 512 bits 17.2 / 19.9, 512 frames 19.4 / 23.2, 1024 20.2 / 24.3, 1500
+// 26.1 / 26.1; of 400 bits 1024 frames 19.4 / 21.2, 1500 23.9 / 22.8; of 600
+// bits (split in two) one frame 20.6 / 19.5, 1024 26.2 / 26.1; of 1001 bits one
+// 25.6 / 22.7, 512 31.7 / 27.5.  The lines are one radix-2 wavefront per SIMD
+// and the shortest split frame.
 int open_radix(const mivit_code& c, int dtype, const std::vector<Item>& items) {
   if (dtype != MIVIT_I8 || !packed_ok(c)) return 2;
   int dev = 0, cus = 0, longest = 0;
@@ -376,7 +383,7 @@ int open_radix(const mivit_code& c, int dtype, const std::vector<Item>& items) {
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 4;
   const int64_t waves = ((int64_t)items.size() << (c.K - 1)) / 64;
-  return waves <= 4 * (int64_t)cus && longest < 4 * kSplitMinIt ? 2 : 4;
+  return waves <= 4 * (int64_t)cus && longest < 4 * kSplitMinItFew ? 2 : 4;
 }
 
 // Build one part: kernel per item, groups, wave and pair tables, survivor
@@ -482,12 +489,16 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
           slots = (int64_t)cus * 4 * (kern == kKernRot4Q ? kSplitWavesPerSimdQ : kSplitWavesPerSimd);
         for (const int2& w : waves) total_it += items[w.x].n_stages >> 1;
       }
+      // half the slots filled by parts of min_it iterations, or the shortest
+      const int64_t min_it =
+          slots > 0 ? std::clamp<int64_t>(2 * total_it / slots, kSplitMinItFew, kSplitMinIt)
+                    : kSplitMinIt;
       for (const int2& w : waves) {
         const int n_it = items[w.x].n_stages >> 1;
         int64_t want = 1;
         if (slots > 0 && total_it > 0) want = ((int64_t)n_it * slots + total_it - 1) / total_it;
         const int P = (int)std::max<int64_t>(
-            1, std::min<int64_t>(want, std::min(kSplitMaxParts, n_it / kSplitMinIt)));
+            1, std::min<int64_t>(want, std::min<int64_t>(kSplitMaxParts, n_it / min_it)));
         SplitUnit u;
         u.first = w.x;
         u.count = w.y;

@@ -40,7 +40,7 @@ def _run(code, fr, x, radix, n_bits, **kw):
 
 # (lengths, packed by choice): one frame on both sides of the shortest split
 # one; counts on both sides of one radix-2 wavefront per SIMD (256 CUs)
-CASES = {"short": ([1], False), "odd": ([1535, 7, 1], False), "split": ([1536], True),
+CASES = {"short": ([1], False), "odd": ([575, 7, 1], False), "split": ([576], True),
          "long": ([5001, 20], True), "few": ([40] * 1024, False), "many": ([40] * 1100, True)}
 
 
