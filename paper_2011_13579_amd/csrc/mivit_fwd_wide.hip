@@ -205,6 +205,7 @@ __global__ __launch_bounds__(64 * wide::kWideWaves, 3) void k_fwd_wide(
   if (kind == 0 && U.part > 0) {
     cx.v_start = bounds[U.bnd + U.part - 1].v_start;
     cx.m_start = &bounds[U.bnd + U.part - 1].m_start;
+    if (lane == 0) bounds[U.bnd + U.part - 1].it_at = U.it_begin;
   }
   T lv[BETA];
   {

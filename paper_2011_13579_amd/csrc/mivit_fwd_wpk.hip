@@ -426,7 +426,10 @@ __device__ __forceinline__ void unit(const DevCode& c, const Item& it, const Spl
 #pragma unroll
       for (int v = 0; v < V; ++v) B.v_start[64 * v + lane] = (int32_t)F.pm[v];
       const int64_t m = W::kC - c_init + taken(F.par_ahead);
-      if (lane == 0) B.m_start = m;
+      if (lane == 0) {
+        B.m_start = m;
+        B.it_at = t_b;
+      }
     }
     for (; t0 + W::kTrip <= t_e; t0 += W::kTrip) {
       if (slot >= 0) fair_share(slot, (t0 - t_s) / W::kTrip);

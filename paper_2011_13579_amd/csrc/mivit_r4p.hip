@@ -498,6 +498,7 @@ __device__ __forceinline__ void fwd_pk_unit(const DevCode& c, const Item* __rest
         B.m_start[2 * m] = m0(0, t_b);
         B.m_start[2 * m + 1] = m0(1, t_b);
       }
+      if (lane == 0) B.it_at = U.it_begin;
     }
     for (; t0 + W::kTrip <= t_e; t0 += W::kTrip) {
       if (slot >= 0) fair_share(slot, (t0 - t_s) / W::kTrip);

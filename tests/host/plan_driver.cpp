@@ -1,0 +1,185 @@
+// The library's host code (mivit_api.cpp) over a HIP runtime and kernel
+// launchers that only keep count: device memory is host memory, a launch
+// records what was launched.  Each scenario prints "name value" lines that
+// tests/test_plan_host.py compares.
+#include <hip/hip_runtime_api.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "../../include/mivit.h"
+#include "../../paper_2011_13579_amd/csrc/mivit_device.h"
+
+namespace {
+int64_t n_malloc, n_copied, in_use;
+std::map<void*, size_t> blocks;
+std::string launches;  // forward launches since the last reset
+}  // namespace
+
+extern "C" {
+hipError_t hipMalloc(void** p, size_t n) {
+  ++n_malloc;
+  *p = std::calloc(1, n ? n : 1);
+  blocks[*p] = n;
+  in_use += (int64_t)n;
+  return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+  if (!p) return hipSuccess;
+  auto it = blocks.find(p);
+  if (it == blocks.end()) {
+    std::printf("hipFree of memory that was not allocated\n");
+    std::abort();
+  }
+  in_use -= (int64_t)it->second;
+  blocks.erase(it);
+  std::free(p);
+  return hipSuccess;
+}
+hipError_t hipMemcpy(void* d, const void* s, size_t n, hipMemcpyKind) {
+  n_copied += (int64_t)n;
+  std::memcpy(d, s, n);
+  return hipSuccess;
+}
+hipError_t hipGetDevice(int* d) { return *d = 0, hipSuccess; }
+hipError_t hipSetDevice(int) { return hipSuccess; }
+hipError_t hipGetDeviceCount(int* n) { return *n = 1, hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceSynchronize() { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { return *v = 256, hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { return *s = nullptr, hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipErrorUnknown; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t*) { return hipErrorUnknown; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  return hipErrorUnknown;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorUnknown; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = nullptr, hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = nullptr, hipSuccess; }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+}
+
+namespace mivit {
+static hipError_t launched(const std::string& what) {
+  launches += (launches.empty() ? "" : " ") + what;
+  return hipSuccess;
+}
+hipError_t launch_fwd(int radix, int, int, const DevCode*, const Item*, int, const void*, uint64_t*,
+                      void*, int32_t*, int32_t*, hipStream_t) {
+  return launched("generic" + std::to_string(radix));
+}
+hipError_t launch_grad(const DevCode*, const GradFrame*, int, int, const uint32_t*, const float*,
+                       float*, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t launch_quant(const float*, int8_t*, int64_t, float, hipStream_t) { return hipSuccess; }
+hipError_t launch_fwd_rot(int, int, int, int, const DevCode*, const Item*, const int2*, int,
+                          const void*, uint64_t*, void*, int32_t*, int32_t*, int32_t*, int,
+                          hipStream_t) {
+  return launched("rot");
+}
+hipError_t launch_fwd_wide(int, int, int, int wpf, bool packed, const DevCode*, const Item*,
+                           const SplitUnit*, int, const void*, uint64_t*, void*, int32_t*,
+                           int32_t*, WideBound*, int64_t*, const SplitUnit*, int, int64_t*,
+                           SplitUnit*, int32_t*, hipStream_t) {
+  return launched((packed ? "wpk" : "wide") + std::to_string(wpf));
+}
+hipError_t launch_fwd_r4p(int, const DevCode*, const Item*, const SplitUnit*, int, const int8_t*,
+                          uint64_t*, int64_t*, int32_t*, int32_t*, int32_t*, int, R4Bound*,
+                          int64_t*, const SplitUnit*, int, int64_t*, hipStream_t) {
+  return launched("r4p");
+}
+hipError_t launch_fwd_r4q(const DevCode*, const Item*, const SplitUnit*, int, const int8_t*,
+                          uint64_t*, int64_t*, int32_t*, int32_t*, int32_t*, int, R4Bound*,
+                          int64_t*, const SplitUnit*, int, int64_t*, hipStream_t) {
+  return launched("r4q");
+}
+hipError_t launch_fwd_r4_mfma(const MfmaGroups&, const DevCode*, const Item*, int, const int8_t*,
+                              uint64_t*, int64_t*, int32_t*, int32_t*, hipStream_t) {
+  return launched("mfma");
+}
+hipError_t launch_tb_seg(int, const DevCode*, const Item*, int, const uint64_t*, const int32_t*,
+                         uint32_t*, int, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t launch_tb_r4p(int, const Item*, const int2*, int, const uint64_t*, const int32_t*,
+                         uint32_t*, int, hipStream_t) {
+  return hipSuccess;
+}
+hipError_t launch_zero_i32(int32_t*, int, hipStream_t) { return hipSuccess; }
+hipError_t launch_fill_random(void*, int64_t, int, uint32_t, hipStream_t) { return hipSuccess; }
+bool mfma_groups(int, int, const uint32_t*, MfmaGroups*) { return false; }
+}  // namespace mivit
+
+namespace {
+
+mivit_code code(int K, std::vector<uint32_t> gens) {
+  mivit_code c;
+  std::memset(&c, 0, sizeof c);
+  c.K = K;
+  c.beta = (int32_t)gens.size();
+  for (size_t b = 0; b < gens.size(); ++b) c.gen[b] = gens[b];
+  return c;
+}
+const mivit_code kK5 = code(5, {023, 035}), kK7 = code(7, {0133, 0171}),
+                 kK8 = code(8, {0247, 0371}), kK9 = code(9, {0557, 0663, 0711}),
+                 kK9r4 = code(9, {0463, 0535, 0733, 0745});
+
+mivit_opts opts(int dtype, int radix) {
+  mivit_opts o;
+  std::memset(&o, 0, sizeof o);
+  o.dtype = dtype;
+  o.radix = radix;
+  return o;
+}
+
+std::vector<mivit_frame> frames(const mivit_code& c, int n, int stages) {
+  std::vector<mivit_frame> f((size_t)n);
+  for (int k = 0; k < n; ++k) {
+    std::memset(&f[k], 0, sizeof f[k]);
+    f[k].llr_offset = (int64_t)k * stages * c.beta;
+    f[k].bit_offset = (int64_t)k * ((stages + 31) / 32) * 32;
+    f[k].n_stages = f[k].n_out = stages;
+    f[k].flags = MIVIT_START_KNOWN;
+  }
+  return f;
+}
+
+// Allocations of, and bytes copied by, the creation of a plan over n frames.
+void tables(const char* name, const mivit_code& c, int dtype, int radix, int n, int stages) {
+  const mivit_opts o = opts(dtype, radix);
+  const std::vector<mivit_frame> f = frames(c, n, stages);
+  const int64_t before = in_use;
+  n_malloc = n_copied = 0;
+  mivit_plan* p = nullptr;
+  const mivit_status s = mivit_plan_create(&p, &c, 1, f.data(), n, &o);
+  std::printf("tables.%s.status %d\n", name, (int)s);
+  std::printf("tables.%s.allocations %lld\n", name, (long long)n_malloc);
+  std::printf("tables.%s.copied %lld\n", name, (long long)n_copied);
+  if (p) mivit_plan_destroy(p);
+  std::printf("tables.%s.left %lld\n", name, (long long)(in_use - before));
+}
+
+}  // namespace
+
+int main() {
+  tables("k7_split", kK7, MIVIT_I8, 4, 128, 2176);
+  tables("k7_open", kK7, MIVIT_I8, 0, 512, 4000);
+  tables("k7_float", kK7, MIVIT_F32, 0, 512, 4000);
+  tables("k9_split", kK9, MIVIT_I8, 0, 512, 4000);
+  tables("k9_rate_quarter", kK9r4, MIVIT_I8, 0, 512, 4000);
+  std::printf("done 1\n");
+  return 0;
+}

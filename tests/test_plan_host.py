@@ -1,0 +1,51 @@
+"""The host side of plans, on the CPU: mivit_api.cpp built for the host alone,
+over a stand-in HIP runtime and stand-in launchers (tests/host/plan_driver.cpp)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = shutil.which("hipcc")
+CLANG = "/opt/rocm/lib/llvm/bin/clang++"
+pytestmark = pytest.mark.skipif(HIPCC is None or not os.path.exists(CLANG),
+                                reason="ROCm compilers not available")
+
+
+@pytest.fixture(scope="module")
+def out(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("plan_host")
+    objs, procs = [], []
+    for s in ("paper_2011_13579_amd/csrc/mivit_api.cpp", "tests/host/plan_driver.cpp"):
+        o = str(tmp / (os.path.splitext(os.path.basename(s))[0] + ".o"))
+        objs.append(o)
+        procs.append(subprocess.Popen(
+            [HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-c",
+             os.path.join(ROOT, s), "-o", o], stderr=subprocess.PIPE, text=True))
+    for p in procs:
+        _, err = p.communicate(timeout=600)
+        assert p.returncode == 0, err[-4000:]
+    exe = str(tmp / "plan_driver")
+    subprocess.run([CLANG] + objs + ["-o", exe], check=True, capture_output=True, text=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
+    values = dict(ln.split(" ", 1) for ln in r.stdout.splitlines())
+    assert values["done"] == "1"
+    return values
+
+
+@pytest.mark.parametrize("name,frames,parts", [
+    ("k7_split", 64, 7), ("k7_open", 256, 8), ("k7_float", 512, 1), ("k9_split", 512, 8),
+    ("k9_rate_quarter", 512, 8)])
+def test_plan_creation_copies_tables_only(out, name, frames, parts):
+    """A plan costs a call that builds one (the first decode of a shape, the
+    first push of a stream) its allocations and copies: one allocation per part
+    beside the plan's two, and no more bytes than the tables that the host
+    writes: per item 64 bytes and its 40 of gradient facts, per wavefront entry
+    a unit of 32 for each of up to `parts` parts and the entry itself, and 16
+    for the traceback."""
+    assert out["tables.%s.status" % name] == "0"
+    assert int(out["tables.%s.allocations" % name]) <= 3
+    assert int(out["tables.%s.copied" % name]) <= 1024 + 512 * 104 + frames * (32 * (parts + 1) + 32)
+    assert out["tables.%s.left" % name] == "0"
