@@ -262,26 +262,29 @@ void free_part(Part& q) {
   q = Part();
 }
 
-// Lays out the device memory of a part: the tables that the host writes, then
-// what only kernels write.  One allocation and one copy, because a call that
-// builds its plan (the first decode of a shape, the first push of a stream)
-// waits for each: with up to fourteen allocations and eight copies, and with
-// zeroed boundary records among them, a decoder's first push of 2^18 K = 7
-// stages in windows of 2048 took 625 us (280 now), the first decode of 512
-// frames of 4000 bits 741 (310).
+// Lays out the device memory of a part: the survivors, the tables that the host
+// writes, then what else only kernels write.  One allocation and one copy,
+// because a call that builds its plan (the first decode of a shape, the first
+// push of a stream) waits for each: with up to fourteen allocations and eight
+// copies, and with zeroed boundary records among them, a decoder's first push of
+// 2^18 K = 7 stages in windows of 2048 took 625 us (280 now), the first decode of
+// 512 frames of 4000 bits 741 (310).  The survivors come first, at the alignment
+// of the allocation itself: a page further on, 4096 frames of 8192 bits of K = 4
+// codes took 3 to 7% longer.
 class PartMemory {
  public:
+  // Memory that no copy fills: before the first table, or after the last.
+  template <typename T>
+  void scratch(T** dst, int64_t n) {
+    if (n > 0) place((void**)dst, (size_t)n * sizeof(T));
+  }
   template <typename T>
   void table(T** dst, const std::vector<T>& v) {
     if (v.empty()) return;
-    const size_t off = place((void**)dst, v.size() * sizeof(T), 256);
-    image_.resize(end_);
-    std::memcpy(image_.data() + off, v.data(), v.size() * sizeof(T));
-  }
-  // (after the last table)
-  template <typename T>
-  void scratch(T** dst, int64_t n, size_t align = 256) {
-    if (n > 0) place((void**)dst, (size_t)n * sizeof(T), align);
+    const size_t off = place((void**)dst, v.size() * sizeof(T));
+    if (image_.empty()) image_at_ = off;
+    image_.resize(end_ - image_at_);
+    std::memcpy(image_.data() + (off - image_at_), v.data(), v.size() * sizeof(T));
   }
   hipError_t commit(void** mem) {
     *mem = nullptr;
@@ -290,19 +293,20 @@ class PartMemory {
     if (e != hipSuccess) return e;
     for (const auto& r : refs_) *r.first = (char*)*mem + r.second;
     return image_.empty() ? hipSuccess
-                          : hipMemcpy(*mem, image_.data(), image_.size(), hipMemcpyHostToDevice);
+                          : hipMemcpy((char*)*mem + image_at_, image_.data(), image_.size(),
+                                      hipMemcpyHostToDevice);
   }
 
  private:
-  size_t place(void** dst, size_t bytes, size_t align) {
-    const size_t off = (end_ + align - 1) / align * align;
+  size_t place(void** dst, size_t bytes) {
+    const size_t off = (end_ + 255) / 256 * 256;
     end_ = off + bytes;
     refs_.push_back({dst, off});
     return off;
   }
-  std::vector<char> image_;
+  std::vector<char> image_;  // the tables, at image_at_ of the allocation
+  size_t image_at_ = 0, end_ = 0;
   std::vector<std::pair<void**, size_t>> refs_;
-  size_t end_ = 0;
 };
 
 void free_plan(mivit_plan* p) {
@@ -479,6 +483,10 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   std::vector<int2> waves, pairs;
   std::vector<SplitUnit> units, split;
   int n_bounds = 0;  // boundary records, written by the forward kernels
+  auto add_split = [&](SplitUnit u) {  // u: part 0, the last unit listed
+    u.warm = (int)units.size() - 1;
+    split.push_back(u);
+  };
   std::vector<char> pair_hi(items.size(), 0);
   if (kern == kKernRot2 || kern == kKernRot4P || kern == kKernRot4Q) {
     const bool packed = kern != kKernRot2;
@@ -551,7 +559,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
           u.it_end = end;
           u.warm = k == 0 ? 0 : std::min(kSplitWarm, prev);
           units.push_back(u);
-          if (k == 0 && P > 1) split.push_back(u);
+          if (k == 0 && P > 1) add_split(u);
           prev = end;
         }
         n_bounds += P - 1;
@@ -610,7 +618,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
         u.it_end = end;
         u.warm = p == 0 ? 0 : std::min(warm, prev);
         units.push_back(u);
-        if (p == 0 && P > 1) split.push_back(u);
+        if (p == 0 && P > 1) add_split(u);
         prev = end;
       }
       n_bounds += P - 1;
@@ -665,6 +673,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
   q.n_units = (int)units.size();
   q.n_split = (int)split.size();
   PartMemory mem;
+  if (!items.empty()) mem.scratch(&q.d_surv, words_total);
   mem.table(&q.d_items, items);
   mem.table(&q.d_waves, waves);
   mem.table(&q.d_tb, tbw);
@@ -685,7 +694,6 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
       mem.scratch(&q.d_rep_count, 1);
     }
   }
-  if (n_items > 0) mem.scratch(&q.d_surv, words_total, 4096);
   q.items = std::move(items);
   const hipError_t e = mem.commit(&q.d_mem);
   if (e != hipSuccess) {

@@ -48,7 +48,7 @@ constexpr int kMaxSplitParts = 8;
 struct SplitUnit {
   int32_t first, count;
   int32_t it_begin, it_end;
-  int32_t warm;
+  int32_t warm;  // (in the list of split entries: index of part 0 among all units)
   int32_t part, n_parts;
   int32_t bnd;  // split entries: index of the entry's first boundary record, else -1
 };
@@ -64,21 +64,17 @@ struct R4Bound {
   uint32_t v_end[256];    // part k at its end
   int64_t m_start[8];
   int64_t m_end[8];
-  int32_t it_at;         // the boundary's iteration (part k+1's it_begin)
-  int32_t pad;
 };
 
 // Boundary k of a frame split in time in the K = 8, 9 radix-2 kernel: the
 // metric of every position (2^(K-1), lane + 64 r) after the range control
-// at stage it_at, for part k at its end and part k+1 after its warm-up, and
+// there, for part k at its end and part k+1 after its warm-up, and
 // each part's metric of state 0 there from its own origin.
 struct WideBound {
   int32_t v_start[256];
   int32_t v_end[256];
   int64_t m_start;
   int64_t m_end;
-  int32_t it_at;
-  int32_t pad;
 };
 
 // Frame facts the gradient kernel needs.

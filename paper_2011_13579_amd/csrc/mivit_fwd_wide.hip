@@ -205,7 +205,6 @@ __global__ __launch_bounds__(64 * wide::kWideWaves, 3) void k_fwd_wide(
   if (kind == 0 && U.part > 0) {
     cx.v_start = bounds[U.bnd + U.part - 1].v_start;
     cx.m_start = &bounds[U.bnd + U.part - 1].m_start;
-    if (lane == 0) bounds[U.bnd + U.part - 1].it_at = U.it_begin;
   }
   T lv[BETA];
   {
@@ -252,7 +251,7 @@ __global__ __launch_bounds__(64 * wide::kWideWaves, 3) void k_fwd_wide(
 // boundary from the true metrics.
 __global__ __launch_bounds__(64 * wide::kWideWaves) void k_wide_check(
     const DevCode* __restrict__ codes, const Item* __restrict__ items,
-    const SplitUnit* __restrict__ split, int n_split,
+    const SplitUnit* __restrict__ split, int n_split, const SplitUnit* __restrict__ units,
     const WideBound* __restrict__ bounds, const int64_t* __restrict__ last_m, int64_t* rep_m0,
     SplitUnit* rep_units, int32_t* rep_count, int64_t* metric) {
   const int lane = threadIdx.x & 63;
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(64 * wide::kWideWaves) void k_wide_check(
   }
   rep_m0[it.slot] = T;
   SplitUnit R = U;
-  R.it_begin = bounds[U.bnd + fail].it_at;
+  R.it_begin = units[U.warm + fail + 1].it_begin;
   R.it_end = it.n_stages;
   R.warm = 0;
   R.part = fail + 1;
@@ -338,8 +337,8 @@ hipError_t launch_fwd_wide(int K, int beta, int dt, int wpf, bool packed, const 
     e = launch_zero_i32(rep_count, 1, st);                                                        \
     if (e != hipSuccess) return e;                                                                \
     hipLaunchKernelGGL(k_wide_check, grid_rep, block, 0, st, codes, items, split, n_split,        \
-                       (const WideBound*)bounds, (const int64_t*)last_m, rep_m0, rep_units,       \
-                       rep_count, (int64_t*)metric);                                              \
+                       units, (const WideBound*)bounds, (const int64_t*)last_m, rep_m0,           \
+                       rep_units, rep_count, (int64_t*)metric);                                   \
     e = hipGetLastError();                                                                        \
     if (e != hipSuccess) return e;                                                                \
     hipLaunchKernelGGL((k_fwd_wide<KM1, 4>), grid_rep, block, 0, st, codes, items,               \

@@ -426,10 +426,7 @@ __device__ __forceinline__ void unit(const DevCode& c, const Item& it, const Spl
 #pragma unroll
       for (int v = 0; v < V; ++v) B.v_start[64 * v + lane] = (int32_t)F.pm[v];
       const int64_t m = W::kC - c_init + taken(F.par_ahead);
-      if (lane == 0) {
-        B.m_start = m;
-        B.it_at = t_b;
-      }
+      if (lane == 0) B.m_start = m;
     }
     for (; t0 + W::kTrip <= t_e; t0 += W::kTrip) {
       if (slot >= 0) fair_share(slot, (t0 - t_s) / W::kTrip);
@@ -513,7 +510,8 @@ __global__ __launch_bounds__(64 * wpk::kWaves, 4) void k_fwd_wpk(
 template <int N, int BETA>
 __global__ __launch_bounds__(64 * wpk::kWaves, 4) void k_wpk_check(
     const DevCode* __restrict__ codes, const Item* __restrict__ items,
-    const SplitUnit* __restrict__ split, int n_split, WideBound* bounds,
+    const SplitUnit* __restrict__ split, int n_split, const SplitUnit* __restrict__ units,
+    WideBound* bounds,
     const int64_t* __restrict__ last_m, int64_t* rep_m0, const int8_t* __restrict__ llr,
     uint64_t* __restrict__ surv, int64_t* metric, int32_t* end_out, int32_t* item_end) {
   using W = wpk::Fwd<N, BETA>;
@@ -549,7 +547,7 @@ __global__ __launch_bounds__(64 * wpk::kWaves, 4) void k_wpk_check(
   }
   if (lane == 0) rep_m0[it.slot] = T;
   __threadfence();
-  U.it_begin = bounds[U.bnd + fail].it_at;
+  U.it_begin = units[U.warm + fail + 1].it_begin;
   U.it_end = it.n_stages;
   U.warm = 0;
   U.part = fail + 1;
@@ -571,8 +569,8 @@ static hipError_t wpk_launch(const DevCode* codes, const Item* items, const Spli
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || n_split <= 0) return e;
   hipLaunchKernelGGL((k_wpk_check<N, BETA>), dim3((n_split + wpk::kWaves - 1) / wpk::kWaves),
-                     block, 0, st, codes, items, split, n_split, bounds, (const int64_t*)last_m,
-                     rep_m0, llr, surv, metric, end_out, item_end);
+                     block, 0, st, codes, items, split, n_split, units, bounds,
+                     (const int64_t*)last_m, rep_m0, llr, surv, metric, end_out, item_end);
   return hipGetLastError();
 }
 

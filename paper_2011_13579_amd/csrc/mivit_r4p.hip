@@ -498,7 +498,6 @@ __device__ __forceinline__ void fwd_pk_unit(const DevCode& c, const Item* __rest
         B.m_start[2 * m] = m0(0, t_b);
         B.m_start[2 * m + 1] = m0(1, t_b);
       }
-      if (lane == 0) B.it_at = U.it_begin;
     }
     for (; t0 + W::kTrip <= t_e; t0 += W::kTrip) {
       if (slot >= 0) fair_share(slot, (t0 - t_s) / W::kTrip);
@@ -654,10 +653,10 @@ __device__ __forceinline__ EntryCheck check_entry(const SplitUnit& U,
 
 // The repair unit of an entry whose boundary `fail` is inexact: the frames
 // from that boundary to their end, from the metrics part `fail` left there.
-__device__ __forceinline__ SplitUnit repair_unit(const SplitUnit& U, const R4Bound* bounds,
+__device__ __forceinline__ SplitUnit repair_unit(const SplitUnit& U, const SplitUnit* units,
                                                  int fail, int n_stages) {
   SplitUnit R = U;
-  R.it_begin = bounds[U.bnd + fail].it_at;
+  R.it_begin = units[U.warm + fail + 1].it_begin;
   R.it_end = n_stages >> 1;
   R.warm = 0;
   R.part = fail + 1;
@@ -669,9 +668,10 @@ __device__ __forceinline__ SplitUnit repair_unit(const SplitUnit& U, const R4Bou
 template <int N, int LB>
 __global__ __launch_bounds__(64 * kPkWaves, N - LB == 2 ? 2 : 4) void k_pk_check(
     const DevCode* __restrict__ codes, const Item* __restrict__ items,
-    const SplitUnit* __restrict__ split, int n_split, R4Bound* bounds,
-    const int64_t* __restrict__ last_m, int64_t* rep_m0, const int8_t* __restrict__ llr,
-    uint64_t* __restrict__ surv, int64_t* metric, int32_t* end_out, int32_t* item_end) {
+    const SplitUnit* __restrict__ split, int n_split, const SplitUnit* __restrict__ units,
+    R4Bound* bounds, const int64_t* __restrict__ last_m, int64_t* rep_m0,
+    const int8_t* __restrict__ llr, uint64_t* __restrict__ surv, int64_t* metric,
+    int32_t* end_out, int32_t* item_end) {
   __shared__ __align__(16) uint32_t tbl_all[kPkWaves][3 * pk::Fwd<N, LB>::kBuf];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int e = __builtin_amdgcn_readfirstlane(blockIdx.x * kPkWaves + wid);
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(64 * kPkWaves, N - LB == 2 ? 2 : 4) void k_pk_check
   }
   if (mine) rep_m0[it.slot] = c.T;
   __threadfence();
-  fwd_pk_wave<N, LB>(codes, items, repair_unit(U, bounds, c.fail, items[U.first].n_stages), 1,
+  fwd_pk_wave<N, LB>(codes, items, repair_unit(U, units, c.fail, items[U.first].n_stages), 1,
                      bounds, const_cast<int64_t*>(last_m), rep_m0, llr, surv, metric, end_out,
                      item_end, tbl_all[wid], lane);
 }
@@ -712,8 +712,8 @@ hipError_t pk_launch(const DevCode* codes, const Item* items, const SplitUnit* u
   if (e != hipSuccess || n_split <= 0) return e;
   const int ns = (n_split + kPkWaves - 1) / kPkWaves;
   hipLaunchKernelGGL((k_pk_check<N, LB>), dim3(ns), dim3(threads), 0, st, codes, items, split,
-                     n_split, bounds, (const int64_t*)last_m, rep_m0, llr, surv, metric, end_out,
-                     item_end);
+                     n_split, units, bounds, (const int64_t*)last_m, rep_m0, llr, surv, metric,
+                     end_out, item_end);
   return hipGetLastError();
 }
 
