@@ -848,8 +848,17 @@ __device__ __forceinline__ void fwd_rot_valu_wave(const DevCode* __restrict__ co
 // One wavefront per wave-table entry, or (counter != nullptr) a persistent
 // grid whose wavefronts take entries in table order (longest frames first)
 // from a device counter that starts at zero, until the table is exhausted.
+//
+// Wavefronts per SIMD the registers are held to, MODE 2: five, but four for
+// rate 1/4 with K = 6, 7, whose periods would reload spilled registers (forward
+// pass, 10000 wavefronts of 517 stages, five / four per SIMD: K = 6 rate 1/4
+// float32 94 / 75 us, float16 130 / 76; K = 7 rate 1/4 float16 77 / 72).  The
+// other codes spill around their periods only, which a full device hides (4096
+// frames of 8192 bits, decode, five / four: K = 4 rate 1/2 float32 183 / 196,
+// K = 5 rate 1/4 int8 271 / 291, K = 5 rate 1/2 float32 177 / 184).
+constexpr int rot_occupancy(int KM1, int BETA) { return KM1 >= 5 && BETA == 4 ? 4 : 5; }
 template <int KM1, int DT, int BETA, int MODE>
-__global__ __launch_bounds__(64 * kRotWaves, MODE == 2 ? 5 : 1) void k_fwd_rot(const DevCode* __restrict__ codes,
+__global__ __launch_bounds__(64 * kRotWaves, MODE == 2 ? rot_occupancy(KM1, BETA) : 1) void k_fwd_rot(const DevCode* __restrict__ codes,
                                                 const Item* __restrict__ items,
                                                 const int2* __restrict__ waves, int n_waves,
                                                 const void* __restrict__ llr_v,
