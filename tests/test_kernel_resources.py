@@ -50,3 +50,8 @@ def test_rotating_kernel_keeps_its_registers(tmp_path, km1, dt, beta):
     (spill, waves), = _resources(tmp_path, ROT % (km1, dt, beta)).values()
     assert spill <= 16 and waves >= 4
 
+
+def test_rate_quarter_k9_fills_the_simds(tmp_path):
+    """Plans cut int8 K = 9 batches into four wavefronts per SIMD."""
+    res = _resources(tmp_path, '#include "mivit_fwd_wide.hip"\n')
+    assert res[(8, 4)] == (0, 4)
