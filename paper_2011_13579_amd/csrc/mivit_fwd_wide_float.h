@@ -32,6 +32,13 @@ namespace mivit {
 
 namespace wide {
 
+// A wavefront's table: 32 rows of 2^BETA patterns, stored by 16 bytes (rate 1/2:
+// by words, as the compiler combines them best).
+template <int BETA>
+struct alignas(BETA == 2 ? alignof(float) : 16) WfTable {
+  float w[32 << BETA];
+};
+
 template <int KM1, int DT, int BETA, int WPF>
 struct Wf {
   using In = typename Ty<DT>::In;
@@ -59,20 +66,42 @@ struct Wf {
   }
 };
 
-// Table rows of a half block (half: 0 or 1), every row written by four lanes.
+// Table rows of a half block (half: 0 or 1): stage (lane & 15), four patterns
+// per lane, bits 2 and 3 of the pattern being bits 4 and 5 of the lane (rates 1/2
+// and 1/3: some lanes write alike).  With whole rows per lane, each written by
+// four lanes, rate 1/4 frames over four wavefronts took 1.6 times as long (K =
+// 9, 4096 of 4096 bits, forward: 1584 us, 977 now).
 template <int KM1, int DT, int BETA, int WPF>
 __device__ __forceinline__ void wf_table(Wf<KM1, DT, BETA, WPF>& F, const float (&lr)[BETA],
                                          int half) {
   constexpr int NP = 1 << BETA;
   float mag = 0.0f;
   float* row = F.bmt + (16 * half + (F.lane & 15)) * NP;
+  float4 w;
 #pragma unroll
-  for (int p = 0; p < NP / 2; ++p) {
+  for (int p = 0; p < 2; ++p) {
     float v = 0.0f;
 #pragma unroll
-    for (int b = 0; b < BETA; ++b) v += ((p >> b) & 1) ? -lr[b] : lr[b];
-    row[p] = v;
-    row[NP - 1 - p] = -v;
+    for (int b = 0; b < 2; ++b) v += ((p >> b) & 1) ? -lr[b] : lr[b];
+    if constexpr (BETA == 2) {
+      row[p] = v;
+      row[NP - 1 - p] = -v;
+    } else {
+      (p ? w.y : w.x) = v;
+      (p ? w.z : w.w) = -v;
+    }
+  }
+  if constexpr (BETA > 2) {
+#pragma unroll
+    for (int b = 2; b < BETA; ++b) {
+      const uint32_t sign = (uint32_t)F.lane << (29 - b) & 0x80000000u;
+      const float x = __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, lr[b]) ^ sign);
+      w.x += x;
+      w.y += x;
+      w.z += x;
+      w.w += x;
+    }
+    *(float4*)(row + ((F.lane >> 2) & (NP - 4))) = w;
   }
 #pragma unroll
   for (int b = 0; b < BETA; ++b) mag += __builtin_fabsf(lr[b]);
@@ -253,10 +282,10 @@ __global__ __launch_bounds__(64 * (WPF == 1 ? wide::kWideWaves : WPF), (1 << (KM
     uint64_t* __restrict__ surv, float* metric, int32_t* end_out, int32_t* item_end) {
   using namespace wide;
   using W = Wf<KM1, DT, BETA, WPF>;
-  constexpr int R = W::R, NS = W::NS, NP = W::NP;
+  constexpr int R = W::R, NS = W::NS;
   constexpr int kWaves = WPF == 1 ? kWideWaves : WPF;
   constexpr int FPB = WPF == 1 ? kWideWaves : 1;  // frames per workgroup
-  __shared__ float bmt_all[kWaves][32 * NP];
+  __shared__ WfTable<BETA> bmt_all[kWaves];
   __shared__ float xpm_all[FPB][NS];
   __shared__ float xch_all[WPF > 1 ? 2 * WPF * 64 * R : 1];
   __shared__ float red_v[WPF];
@@ -275,7 +304,7 @@ __global__ __launch_bounds__(64 * (WPF == 1 ? wide::kWideWaves : WPF), (1 << (KM
   F.fw = fw;
   F.llr = (const typename Ty<DT>::In*)llr_v + it.llr_off;
   F.sv = (uint8_t*)(surv + it.surv_off) + 64 * R * fw + lane;
-  F.bmt = bmt_all[wid];
+  F.bmt = bmt_all[wid].w;
   F.xch = xch_all;
   F.xb = 0;
   F.bad = 0;
