@@ -1017,6 +1017,12 @@ mivit_status mivit_plan_create(mivit_plan** out, const mivit_code* codes, int32_
       for (const Choice& ch : cand) {
         Part q;
         mivit_status s = build_part(codes, frames, by_code[c], o, o.dtype, ch, c, q);
+        if (s == MIVIT_ENOMEM && ch.radix == 0) {
+          // packed frames that share no lane group keep twice radix 2's survivors
+          Choice two = ch;
+          two.radix = 2;
+          s = build_part(codes, frames, by_code[c], o, o.dtype, two, c, q);
+        }
         if (s != MIVIT_OK) throw s;
         const float ms =
             cand.size() > 1 ? time_part(p, q, t_llr, (uint32_t*)t_bits, t_metric, (int32_t*)t_end)

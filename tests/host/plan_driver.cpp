@@ -16,6 +16,7 @@
 
 namespace {
 int64_t n_malloc, n_copied, in_use;
+int64_t memory = INT64_MAX;  // of the device
 std::map<void*, size_t> blocks;
 std::string launches;  // forward launches since the last reset
 }  // namespace
@@ -23,7 +24,9 @@ std::string launches;  // forward launches since the last reset
 extern "C" {
 hipError_t hipMalloc(void** p, size_t n) {
   ++n_malloc;
-  *p = std::calloc(1, n ? n : 1);
+  *p = nullptr;
+  if (in_use + (int64_t)n > memory) return hipErrorOutOfMemory;
+  *p = std::malloc(n ? n : 1);
   blocks[*p] = n;
   in_use += (int64_t)n;
   return hipSuccess;
@@ -172,6 +175,26 @@ void tables(const char* name, const mivit_code& c, int dtype, int radix, int n, 
   std::printf("tables.%s.left %lld\n", name, (long long)(in_use - before));
 }
 
+// A plan that leaves the radix open, over frames of four lengths (which share
+// no packed lane group: twice radix 2's survivors), on a device whose memory
+// holds only the latter.
+void open_radix_memory(const char* name, const mivit_code& c) {
+  const mivit_opts o = opts(MIVIT_I8, 0);
+  std::vector<mivit_frame> f = frames(c, 4, 400000);
+  for (int k = 0; k < 4; ++k) f[k].n_stages -= 1000 * k, f[k].n_out -= 1000 * k;
+  const int64_t before = in_use, stages = 4 * 400000;
+  memory = before + stages * (1 << (c.K - 1)) / 8 * 3 / 2;
+  mivit_plan* p = nullptr;
+  const mivit_status s = mivit_plan_create(&p, &c, 1, f.data(), 4, &o);
+  memory = INT64_MAX;
+  launches.clear();
+  uint32_t word = 0;
+  if (p) mivit_decode(p, &word, &word, nullptr, nullptr, nullptr);
+  std::printf("open_radix_memory.%s %d %s\n", name, (int)s, launches.c_str());
+  if (p) mivit_plan_destroy(p);
+  std::printf("open_radix_memory.%s.left %lld\n", name, (long long)(in_use - before));
+}
+
 }  // namespace
 
 int main() {
@@ -180,6 +203,8 @@ int main() {
   tables("k7_float", kK7, MIVIT_F32, 0, 512, 4000);
   tables("k9_split", kK9, MIVIT_I8, 0, 512, 4000);
   tables("k9_rate_quarter", kK9r4, MIVIT_I8, 0, 512, 4000);
+  open_radix_memory("k7", kK7);
+  open_radix_memory("k5", kK5);
   std::printf("done 1\n");
   return 0;
 }

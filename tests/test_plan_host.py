@@ -49,3 +49,11 @@ def test_plan_creation_copies_tables_only(out, name, frames, parts):
     assert int(out["tables.%s.allocations" % name]) <= 3
     assert int(out["tables.%s.copied" % name]) <= 1024 + 512 * 104 + frames * (32 * (parts + 1) + 32)
     assert out["tables.%s.left" % name] == "0"
+
+
+@pytest.mark.parametrize("code", ["k7", "k5"])
+def test_open_radix_falls_back_to_what_fits(out, code):
+    """Frames of different lengths take twice the survivors in packed radix 4:
+    where that does not fit, a plan that leaves the radix open runs radix 2."""
+    assert out["open_radix_memory." + code] == "0 rot"
+    assert out["open_radix_memory.%s.left" % code] == "0"
