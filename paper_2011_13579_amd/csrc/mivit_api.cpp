@@ -103,6 +103,7 @@ constexpr int kMaxGraphs = 8;  // recorded decode graphs kept per plan
 struct Choice {
   int radix = 2;  // 0: open_radix
   int variant = 0;
+  int waves = 0;  // K = 8, 9 float, variant 0: wavefronts per frame; 0: by the batch
   bool persistent = false;
   bool split = true;  // packed radix 4: split long frame pairs in time
 };
@@ -586,6 +587,7 @@ mivit_status build_part(const mivit_code* codes, const mivit_frame* frames,
     if (!i8)
       g.wpf = ch.variant == 6   ? 2
               : ch.variant == 7 ? 4
+              : ch.waves > 0    ? ch.waves
                                 : wide_waves(c.K, cus, total, items.empty() ? 0 : items[0].n_stages);
     else
       g.two16 = c.beta <= 3;
@@ -784,18 +786,24 @@ hipError_t run_parts(mivit_plan* p, int phases, const void* llr, uint32_t* bits,
 // Candidate kernel choices of a part, for the autotuner.
 std::vector<Choice> candidates(const mivit_code& c, int dtype, int radix) {
   std::vector<Choice> out;
-  auto add = [&](int r, int v, bool pers, bool split = true) {
+  auto add = [&](int r, int v, bool pers, bool split = true, int waves = 0) {
     Choice ch;
     ch.radix = r;
     ch.variant = v;
+    ch.waves = waves;
     ch.persistent = pers;
     ch.split = split;
     out.push_back(ch);
   };
   const bool i8 = dtype == MIVIT_I8;
   if (dtype == MIVIT_F16) {  // the default exchange scheme only
-    add(2, 0, false);
-    if (c.K <= 7) add(2, 0, true);
+    if (c.K <= 7) {
+      add(2, 0, false);
+      add(2, 0, true);
+    } else {  // one wavefront per frame, or as many as hold one register each
+      add(2, 0, false, true, 1);
+      add(2, 0, false, true, 1 << (c.K - 7));
+    }
     return out;
   }
   // K >= 8: variant 0 holds the states in registers, 1 and 2 exchange through LDS
@@ -804,7 +812,9 @@ std::vector<Choice> candidates(const mivit_code& c, int dtype, int radix) {
       for (int v = 0; v < 3; ++v) add(2, v, false);
       add(2, 0, true);
     } else {
-      add(2, 0, false);  // registers (wide kernel)
+      // registers (wide kernel); float: one wavefront per frame, whatever the
+      // batch alone would be given (its parts share the device)
+      add(2, 0, false, true, i8 ? 0 : 1);
       add(2, 1, false);  // LDS exchanges (generic kernel)
       if (dtype == MIVIT_F32) add(2, 6, false);  // registers, two wavefronts per frame
       if (dtype == MIVIT_F32 && c.K == 9) add(2, 7, false);  // four wavefronts per frame

@@ -19,6 +19,8 @@ int64_t n_malloc, n_copied, in_use;
 int64_t memory = INT64_MAX;  // of the device
 std::map<void*, size_t> blocks;
 std::string launches;  // forward launches since the last reset
+float now;             // ms; each forward launch takes what `cost` says
+std::map<std::string, float> cost;
 }  // namespace
 
 extern "C" {
@@ -66,17 +68,20 @@ hipError_t hipGraphInstantiate(hipGraphExec_t*, hipGraph_t, hipGraphNode_t*, cha
   return hipErrorUnknown;
 }
 hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipErrorUnknown; }
-hipError_t hipEventCreate(hipEvent_t* e) { return *e = nullptr, hipSuccess; }
-hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return *e = nullptr, hipSuccess; }
-hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { return *e = (hipEvent_t) new float(0), hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t e) { return delete (float*)e, hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t) { return *(float*)e = now, hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { return *ms = 1.0f, hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
+  return *ms = *(float*)b - *(float*)a, hipSuccess;
+}
 }
 
 namespace mivit {
 static hipError_t launched(const std::string& what) {
   launches += (launches.empty() ? "" : " ") + what;
+  now += cost.count(what) ? cost[what] : 1.0f;
   return hipSuccess;
 }
 hipError_t launch_fwd(int radix, int, int, const DevCode*, const Item*, int, const void*, uint64_t*,
@@ -195,6 +200,23 @@ void open_radix_memory(const char* name, const mivit_code& c) {
   std::printf("open_radix_memory.%s.left %lld\n", name, (long long)(in_use - before));
 }
 
+// What the tuner keeps for four short frames where `fastest` runs fastest.
+void tuned(const char* name, const mivit_code& c, int dtype, const char* fastest) {
+  mivit_opts o = opts(dtype, 0);
+  o.flags = MIVIT_PLAN_AUTOTUNE;
+  const std::vector<mivit_frame> f = frames(c, 4, 300);
+  cost.clear();
+  cost[fastest] = 0.5f;
+  mivit_plan* p = nullptr;
+  const mivit_status s = mivit_plan_create(&p, &c, 1, f.data(), 4, &o);
+  launches.clear();
+  uint32_t word = 0;
+  if (p) mivit_decode(p, &word, &word, nullptr, nullptr, nullptr);
+  std::printf("tuned.%s %d %s\n", name, (int)s, launches.c_str());
+  if (p) mivit_plan_destroy(p);
+  cost.clear();
+}
+
 }  // namespace
 
 int main() {
@@ -205,6 +227,14 @@ int main() {
   tables("k9_rate_quarter", kK9r4, MIVIT_I8, 0, 512, 4000);
   open_radix_memory("k7", kK7);
   open_radix_memory("k5", kK5);
+  for (const char* w : {"wide1", "wide2", "wide4", "generic2"})
+    tuned((std::string("k9_f32.") + w).c_str(), kK9, MIVIT_F32, w);
+  for (const char* w : {"wide1", "wide2", "generic2"})
+    tuned((std::string("k8_f32.") + w).c_str(), kK8, MIVIT_F32, w);
+  for (const char* w : {"wide1", "wide4"})
+    tuned((std::string("k9_f16.") + w).c_str(), kK9, MIVIT_F16, w);
+  for (const char* w : {"wide1", "wide2"})
+    tuned((std::string("k8_f16.") + w).c_str(), kK8, MIVIT_F16, w);
   std::printf("done 1\n");
   return 0;
 }

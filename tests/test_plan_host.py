@@ -57,3 +57,13 @@ def test_open_radix_falls_back_to_what_fits(out, code):
     where that does not fit, a plan that leaves the radix open runs radix 2."""
     assert out["open_radix_memory." + code] == "0 rot"
     assert out["open_radix_memory.%s.left" % code] == "0"
+
+
+@pytest.mark.parametrize("name", ["k9_f32.wide1", "k9_f32.wide2", "k9_f32.wide4", "k9_f32.generic2",
+                                  "k8_f32.wide1", "k8_f32.wide2", "k8_f32.generic2",
+                                  "k9_f16.wide1", "k9_f16.wide4", "k8_f16.wide1", "k8_f16.wide2"])
+def test_tuner_tries_every_form_of_the_float_kernel(out, name):
+    """K = 8, 9 float frames run over one, two or four wavefronts each: the
+    tuner keeps whichever is fastest, also one per frame where the batch alone
+    would be spread over four."""
+    assert out["tuned." + name] == "0 " + name.split(".")[1]
