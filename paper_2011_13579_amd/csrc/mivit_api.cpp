@@ -1245,8 +1245,8 @@ mivit_status mivit_plan_describe(const mivit_plan* p, char* buf, int32_t len) {
                     : table        ? "one wavefront per table entry"
                     : q.ch.variant == 6 ? "two wavefronts per item"
                     : q.ch.variant == 7 ? "four wavefronts per item"
-                    : g.wpf == 2   ? "one wavefront per item half"  // of its states
-                    : g.wpf == 4   ? "one wavefront per item quarter"
+                    : g.wpf == 2   ? "2 wavefronts per item (automatic)"
+                    : g.wpf == 4   ? "4 wavefronts per item (automatic)"
                     : g.two16      ? "one wavefront per item, two states per register"
                                    : "one wavefront per item",
                     g.count, table ? g.n_waves : g.wpf * g.count);

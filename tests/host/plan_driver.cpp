@@ -217,6 +217,21 @@ void tuned(const char* name, const mivit_code& c, int dtype, const char* fastest
   cost.clear();
 }
 
+void described(const char* name, const mivit_code& c, int dtype, int variant, int n) {
+  mivit_opts o = opts(dtype, 0);
+  o.variant = variant;
+  const std::vector<mivit_frame> f = frames(c, n, 300);
+  mivit_plan* p = nullptr;
+  char text[512] = "";
+  if (mivit_plan_create(&p, &c, 1, f.data(), n, &o) == MIVIT_OK)
+    mivit_plan_describe(p, text, sizeof text);
+  launches.clear();
+  uint32_t word = 0;
+  if (p) mivit_decode(p, &word, &word, nullptr, nullptr, nullptr);
+  std::printf("described.%s %s: %s\n", name, launches.c_str(), text);
+  if (p) mivit_plan_destroy(p);
+}
+
 }  // namespace
 
 int main() {
@@ -235,6 +250,12 @@ int main() {
     tuned((std::string("k9_f16.") + w).c_str(), kK9, MIVIT_F16, w);
   for (const char* w : {"wide1", "wide2"})
     tuned((std::string("k8_f16.") + w).c_str(), kK8, MIVIT_F16, w);
+  described("k9_few", kK9, MIVIT_F32, 0, 4);
+  described("k9_many", kK9, MIVIT_F32, 0, 4096);
+  described("k9_v6", kK9, MIVIT_F32, 6, 4);
+  described("k9_v7", kK9, MIVIT_F32, 7, 4);
+  described("k8_few", kK8, MIVIT_F32, 0, 4);
+  described("k8_f16", kK8, MIVIT_F16, 0, 4096);
   std::printf("done 1\n");
   return 0;
 }

@@ -67,3 +67,15 @@ def test_tuner_tries_every_form_of_the_float_kernel(out, name):
     tuner keeps whichever is fastest, also one per frame where the batch alone
     would be spread over four."""
     assert out["tuned." + name] == "0 " + name.split(".")[1]
+
+
+@pytest.mark.parametrize("name,runs,text", [
+    ("k9_few", "wide4", "4 wavefronts per item (automatic), 4 items, 16 wavefronts"),
+    ("k9_many", "wide1", "one wavefront per item, 4096 items, 4096 wavefronts"),
+    ("k9_v6", "wide2", "two wavefronts per item, 4 items, 8 wavefronts"),
+    ("k9_v7", "wide4", "four wavefronts per item, 4 items, 16 wavefronts"),
+    ("k8_few", "wide2", "2 wavefronts per item (automatic), 4 items, 8 wavefronts"),
+    ("k8_f16", "wide1", "one wavefront per item, 4096 items, 4096 wavefronts")])
+def test_description_names_what_runs(out, name, runs, text):
+    assert out["described." + name].startswith(runs + ": ")
+    assert out["described." + name].endswith(text)
