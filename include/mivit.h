@@ -279,11 +279,11 @@ mivit_status mivit_decode_uniform(const void* llr, int32_t dtype, const mivit_co
 /* mivit_decode_uniform for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
  * hipMalloc): same arguments, layout, kernels and results, but the call's
- * tables and survivor memory live in one fixed 64 MiB device array of the
+ * tables and survivor memory live in one fixed 70 MiB device array of the
  * library (each GPU the library runs on holds it until the process ends),
  * and the call allocates nothing and copies nothing from the host: it
  * launches a table kernel, the forward and the traceback kernel.
- *   Limit: about 256 B of tables per frame plus the survivor memory, which
+ *   Limit: 64 MiB of tables, about 256 B per frame, and survivor memory, which
  *   for K <= 7 radix 2 is 2^(K-1)/8 B per stage (whole 32-stage blocks),
  *   for the packed radix-4 kernel 2^(K-1)/8 B per stage and frame (whole
  *   16-stage groups per frame pair), for K = 8, 9 2^(K-1)/8 B per stage

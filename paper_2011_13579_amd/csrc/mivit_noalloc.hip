@@ -1,7 +1,7 @@
 // One-call decode of equal-length frames that allocates no device memory:
 // every table and the survivor memory of the call live in one fixed,
-// file-scope device array of kScratchBytes, which each GPU the library runs
-// on holds until the process ends.  Host code never names the array's
+// file-scope device array (kScratchBytes, plus kTableBytes for the traceback's
+// tables), which each GPU the library runs on holds until the process ends.  Host code never names the array's
 // symbol directly: at the first call on a device (that device current) its
 // device address is read once with hipGetSymbolAddress and kept per device;
 // every kernel receives that address.
@@ -44,10 +44,15 @@ using namespace mivit;
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)64 << 20;
+constexpr size_t kScratchBytes = (size_t)64 << 20;  // what a call's limit is measured against
+// The traceback's wavefronts and frame pairs, eight bytes each, lie behind that
+// and do not count.  A frame within the limit takes 72 bytes of it or more, so
+// the pairs take 3.7 MiB at most; a wavefront's segments have survivors of 16
+// bytes or more each, and it has 32 or 64 unless its frames are that few.
+constexpr size_t kTableBytes = (size_t)6 << 20;
 constexpr int kMaxDevices = 64;
 
-__device__ __align__(256) uint8_t scratch[kScratchBytes];
+__device__ __align__(256) uint8_t scratch[kScratchBytes + kTableBytes];
 
 // kernel families of the one-call path (the choices mivit_decode_uniform's
 // plans make for a uniform batch with default options)
@@ -88,8 +93,9 @@ bool make_layout(const mivit_code& c, int dtype, int F, int S, int n_info, int c
   o = align256(o + (size_t)F * sizeof(Item));
   L.off_waves = o;  // radix 2: (first, count) per entry; else one whole-frame unit per entry
   o = align256(o + (size_t)L.n_waves * (L.fam == kFamRot2 ? sizeof(int2) : sizeof(SplitUnit)));
-  L.off_tb = o;
-  o = align256(o + ((size_t)L.n_tb + L.n_pairs) * sizeof(int2));
+  L.off_tb = kScratchBytes;
+  if (((size_t)L.n_tb + L.n_pairs) * sizeof(int2) > kTableBytes) return false;
+  o = align256(o + (size_t)L.n_pairs * sizeof(int2));  // counted, as ever
   L.off_end = o;
   o = align256(o + (size_t)F * sizeof(int32_t));
   L.off_surv = o;

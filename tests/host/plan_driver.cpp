@@ -1,5 +1,5 @@
-// The library's host code (mivit_api.cpp) over a HIP runtime and kernel
-// launchers that only keep count: device memory is host memory, a launch
+// The library's host code (mivit_api.cpp, mivit_noalloc.hip) over a HIP runtime
+// and kernel launchers that only keep count: device memory is host memory, a launch
 // records what was launched.  Each scenario prints "name value" lines that
 // tests/test_plan_host.py compares.
 #include <hip/hip_runtime_api.h>
@@ -19,6 +19,7 @@ int64_t n_malloc, n_copied, in_use;
 int64_t memory = INT64_MAX;  // of the device
 std::map<void*, size_t> blocks;
 std::string launches;  // forward launches since the last reset
+int64_t tb_end;        // last traceback launch: end of its table, from the items
 float now;             // ms; each forward launch takes what `cost` says
 std::map<std::string, float> cost;
 }  // namespace
@@ -76,7 +77,22 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float* ms, hipEvent_t a, hipEvent_t b) {
   return *ms = *(float*)b - *(float*)a, hipSuccess;
 }
+// the table kernel of mivit_noalloc.hip: nothing is launched
+hipError_t hipGetSymbolAddress(void** p, const void*) { return *p = (void*)256, hipSuccess; }
+hipError_t hipLaunchKernel(const void*, dim3, dim3, void**, size_t, hipStream_t) {
+  return hipSuccess;
 }
+hipError_t __hipPushCallConfiguration(dim3, dim3, size_t, hipStream_t) { return hipSuccess; }
+hipError_t __hipPopCallConfiguration(dim3*, dim3*, size_t*, hipStream_t*) { return hipSuccess; }
+void** __hipRegisterFatBinary(const void*) { return nullptr; }
+void __hipRegisterFunction(void**, const void*, char*, const char*, unsigned, void*, void*, void*,
+                           void*, int*) {}
+void __hipRegisterVar(void**, void*, char*, char*, int, size_t, int, int) {}
+void __hipUnregisterFatBinary(void**) {}
+}
+
+// (the host-only build of mivit_noalloc.hip has no device code to register)
+extern "C" const char __hip_fatbin[8] = {};
 
 namespace mivit {
 static hipError_t launched(const std::string& what) {
@@ -122,8 +138,9 @@ hipError_t launch_tb_seg(int, const DevCode*, const Item*, int, const uint64_t*,
                          uint32_t*, int, hipStream_t) {
   return hipSuccess;
 }
-hipError_t launch_tb_r4p(int, const Item*, const int2*, int, const uint64_t*, const int32_t*,
-                         uint32_t*, int, hipStream_t) {
+hipError_t launch_tb_r4p(int, const Item* items, const int2* table, int n, const uint64_t*,
+                         const int32_t*, uint32_t*, int, hipStream_t) {
+  tb_end = (int64_t)((const char*)(table + n) - (const char*)items);
   return hipSuccess;
 }
 hipError_t launch_zero_i32(int32_t*, int, hipStream_t) { return hipSuccess; }
@@ -232,6 +249,54 @@ void described(const char* name, const mivit_code& c, int dtype, int variant, in
   if (p) mivit_plan_destroy(p);
 }
 
+// The allocation-free call's limit: 64 MiB of items, wavefront entries, frame
+// pairs, end states and survivors, whatever else it keeps.
+int64_t noalloc_bytes(const mivit_code& c, int dtype, int64_t F, int S) {
+  const bool packed = dtype == MIVIT_I8 && c.beta == 2 && (c.K == 5 || c.K == 7);
+  const int64_t fpw = packed ? 2 * (64 >> (c.K - 1)) : c.K <= 7 ? 64 >> (c.K - 1) : 1;
+  const int64_t waves = (F + fpw - 1) / fpw, pairs = packed ? (F + 1) / 2 : 0;
+  auto up = [](int64_t x) { return (x + 255) / 256 * 256; };
+  int64_t o = up((int64_t)sizeof(mivit::DevCode));
+  o = up(o + F * (int64_t)sizeof(mivit::Item));
+  o = up(o + waves * (int64_t)(packed || c.K > 7 ? sizeof(mivit::SplitUnit) : sizeof(int2)));
+  o = up(o + pairs * (int64_t)sizeof(int2));
+  o = up(o + F * 4);
+  const int64_t ws = packed ? mivit::surv_words_r4p(c.K, S) : mivit::surv_words_blocks32(c.K, S);
+  return o + ((packed ? pairs : F) * ws + mivit::kSurvSlackWords) * 8;
+}
+
+mivit_status uniform(bool noalloc, const mivit_code& c, int dtype, int F, int n) {
+  uint32_t word = 0;
+  launches.clear();
+  return noalloc ? mivit_decode_uniform_noalloc(&word, dtype, &c, F, n, 1, &word, nullptr, nullptr)
+                 : mivit_decode_uniform(&word, dtype, &c, F, n, 1, &word, nullptr, nullptr);
+}
+
+void noalloc_limit(const char* name, const mivit_code& c, int dtype) {
+  int refused = 0, accepted = 0;
+  int64_t room = 0;  // most bytes from the items to the traceback table's end
+  for (int n : {1, 20, 33, 100, 1000, 2048, 20000}) {
+    const int S = n + c.K - 1;
+    int lo = 0, hi = 1 << 22;  // the largest batch within the limit
+    while (hi - lo > 1) {
+      const int mid = lo + (hi - lo) / 2;
+      (noalloc_bytes(c, dtype, mid, S) <= 64 << 20 ? lo : hi) = mid;
+    }
+    refused += uniform(true, c, dtype, lo, n) != MIVIT_OK;
+    if (tb_end > room) room = tb_end;
+    accepted += uniform(true, c, dtype, lo + 1, n) != MIVIT_ENOMEM;
+  }
+  std::printf("noalloc_limit.%s %d %d\n", name, refused, accepted);
+  std::printf("noalloc_room.%s %lld\n", name, (long long)room);
+}
+
+void same_kernel(const char* name, const mivit_code& c, int dtype, int F, int n) {
+  const mivit_status a = uniform(false, c, dtype, F, n);
+  const std::string plan = launches;
+  const mivit_status b = uniform(true, c, dtype, F, n);
+  std::printf("same_kernel.%s %d%d %s %s\n", name, (int)a, (int)b, plan.c_str(), launches.c_str());
+}
+
 }  // namespace
 
 int main() {
@@ -256,6 +321,23 @@ int main() {
   described("k9_v7", kK9, MIVIT_F32, 7, 4);
   described("k8_few", kK8, MIVIT_F32, 0, 4);
   described("k8_f16", kK8, MIVIT_F16, 0, 4096);
+  noalloc_limit("k3_f32", code(3, {7, 5}), MIVIT_F32);
+  noalloc_limit("k4_i8", code(4, {015, 017}), MIVIT_I8);
+  noalloc_limit("k5_i8", kK5, MIVIT_I8);
+  noalloc_limit("k7_i8", kK7, MIVIT_I8);
+  noalloc_limit("k7_f16", kK7, MIVIT_F16);
+  noalloc_limit("k8_i8", kK8, MIVIT_I8);
+  noalloc_limit("k9_f32", kK9, MIVIT_F32);
+  noalloc_limit("k9r4_i8", kK9r4, MIVIT_I8);
+  same_kernel("k7_short", kK7, MIVIT_I8, 1, 500);
+  same_kernel("k7_long", kK7, MIVIT_I8, 1, 600);
+  same_kernel("k7_few", kK7, MIVIT_I8, 1024, 40);
+  same_kernel("k7_many", kK7, MIVIT_I8, 1100, 40);
+  same_kernel("k5_few", kK5, MIVIT_I8, 4096, 40);
+  same_kernel("k5_many", kK5, MIVIT_I8, 4200, 40);
+  same_kernel("k9_i8", kK9, MIVIT_I8, 3, 200);
+  same_kernel("k9_f32", kK9, MIVIT_F32, 3, 200);
+  same_kernel("k8_f32_many", kK8, MIVIT_F32, 3000, 50);
   std::printf("done 1\n");
   return 0;
 }

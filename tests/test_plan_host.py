@@ -1,5 +1,5 @@
-"""The host side of plans, on the CPU: mivit_api.cpp built for the host alone,
-over a stand-in HIP runtime and stand-in launchers (tests/host/plan_driver.cpp)."""
+"""The host side of plans and of the allocation-free call, on the CPU:
+mivit_api.cpp and mivit_noalloc.hip built for the host alone, over a stand-in HIP runtime and stand-in launchers (tests/host/plan_driver.cpp)."""
 import os
 import shutil
 import subprocess
@@ -17,12 +17,15 @@ pytestmark = pytest.mark.skipif(HIPCC is None or not os.path.exists(CLANG),
 def out(tmp_path_factory):
     tmp = tmp_path_factory.mktemp("plan_host")
     objs, procs = [], []
-    for s in ("paper_2011_13579_amd/csrc/mivit_api.cpp", "tests/host/plan_driver.cpp"):
-        o = str(tmp / (os.path.splitext(os.path.basename(s))[0] + ".o"))
-        objs.append(o)
+    for s in ("paper_2011_13579_amd/csrc/mivit_api.cpp",
+              "paper_2011_13579_amd/csrc/mivit_noalloc.hip", "tests/host/plan_driver.cpp"):
+        name = os.path.splitext(os.path.basename(s))[0]
+        objs.append(str(tmp / (name + ".o")))
+        # the one with a kernel: its (absent) device code under a fixed symbol
+        cuid = ["-fuse-cuid=none"] if s.endswith(".hip") else []
         procs.append(subprocess.Popen(
-            [HIPCC, "-x", "hip", "--offload-host-only", "-O1", "-std=c++17", "-c",
-             os.path.join(ROOT, s), "-o", o], stderr=subprocess.PIPE, text=True))
+            [HIPCC, "-x", "hip", "--offload-host-only"] + cuid + ["-O1", "-std=c++17", "-c",
+             os.path.join(ROOT, s), "-o", objs[-1]], stderr=subprocess.PIPE, text=True))
     for p in procs:
         _, err = p.communicate(timeout=600)
         assert p.returncode == 0, err[-4000:]
@@ -79,3 +82,13 @@ def test_tuner_tries_every_form_of_the_float_kernel(out, name):
 def test_description_names_what_runs(out, name, runs, text):
     assert out["described." + name].startswith(runs + ": ")
     assert out["described." + name].endswith(text)
+
+
+@pytest.mark.parametrize("name", ["k3_f32", "k4_i8", "k5_i8", "k7_i8", "k7_f16", "k8_i8", "k9_f32",
+                                  "k9r4_i8"])
+def test_allocation_free_call_takes_what_its_limit_allows(out, name):
+    """The largest batch whose items, entries, pairs, end states and survivors
+    fit 64 MiB is decoded and one frame more is refused: tables that the
+    traceback adds do not count, and end within the array."""
+    assert out["noalloc_limit." + name] == "0 0"
+    assert int(out["noalloc_room." + name]) <= 70 << 20
