@@ -278,7 +278,9 @@ mivit_status mivit_decode_uniform(const void* llr, int32_t dtype, const mivit_co
 
 /* mivit_decode_uniform for callers that cannot allocate device memory
  * (code under HIP graph capture, tight serving loops, harnesses that forbid
- * hipMalloc): same arguments, layout, kernels and results, but the call's
+ * hipMalloc): same arguments, layout and results, and the kernels of
+ * mivit_decode_uniform with every frame whole (few short int8 frames of a K = 5
+ * rate-1/2 code run packed radix 4 here, radix 2 there), but the call's
  * tables and survivor memory live in one fixed 70 MiB device array of the
  * library (each GPU the library runs on holds it until the process ends),
  * and the call allocates nothing and copies nothing from the host: it

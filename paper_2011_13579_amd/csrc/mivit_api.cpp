@@ -117,11 +117,7 @@ struct Choice {
 constexpr int kSplitAlign = 48;
 constexpr int kSplitWarm = 96;
 constexpr int kSplitMinIt = 384;
-// where whole frames leave the device mostly idle, parts may be this short
-// (decode, parts of at least 384 / 144 iterations: 128 windows of 2176 stages
-// 42 / 31 us, 16 frames of 1001 bits 35 / 25, 256 of 2048 38 / 29, 512 of 4096
-// 56 / 51)
-constexpr int kSplitMinItFew = 144;
+// (kSplitMinItFew: where whole frames leave the device mostly idle)
 constexpr int kSplitMaxParts = kMaxSplitParts;
 constexpr int kSplitWavesPerSimd = 4;
 // The four-states-per-lane kernel holds eight frames per wavefront and four
@@ -402,15 +398,7 @@ bool quad_pays(const std::vector<Item>& items) {
   return waves >= 2 * 4 * (int64_t)cus;
 }
 
-// Radix of a part whose plan leaves it open: int8 K = 5, 7 rate-1/2 codes run
-// packed radix 4, except few frames too short to be split in time, which
-// radix 2 runs faster: its wavefronts hold half as many frames and a shorter
-// chain per stage.  Forward and traceback, K = 7, us, radix 2 / packed: one
-// frame of 512 bits 17.2 / 19.9, 512 frames 19.4 / 23.2, 1024 20.2 / 24.3, 1500
-// 26.1 / 26.1; of 400 bits 1024 frames 19.4 / 21.2, 1500 23.9 / 22.8; of 600
-// bits (split in two) one frame 20.6 / 19.5, 1024 26.2 / 26.1; of 1001 bits one
-// 25.6 / 22.7, 512 31.7 / 27.5.  The lines are one radix-2 wavefront per SIMD
-// and the shortest split frame.
+// Radix of a part whose plan leaves it open.
 int open_radix(const mivit_code& c, int dtype, const std::vector<Item>& items) {
   if (dtype != MIVIT_I8 || !packed_ok(c)) return 2;
   int dev = 0, cus = 0, longest = 0;
@@ -418,8 +406,7 @@ int open_radix(const mivit_code& c, int dtype, const std::vector<Item>& items) {
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
     return 4;
-  const int64_t waves = ((int64_t)items.size() << (c.K - 1)) / 64;
-  return waves <= 4 * (int64_t)cus && longest < 4 * kSplitMinItFew ? 2 : 4;
+  return radix4_pays(c.K, cus, (int64_t)items.size(), longest) ? 4 : 2;
 }
 
 // Build one part: kernel per item, groups, wave and pair tables, survivor

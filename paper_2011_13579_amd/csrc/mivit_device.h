@@ -139,6 +139,28 @@ struct GroupEmitter {
   }
 };
 
+// Shortest part, in iterations, that a packed K = 5, 7 frame is cut into where
+// whole frames leave the device mostly idle (decode, parts of at least 384 / 144
+// iterations: 128 windows of 2176 stages 42 / 31 us, 16 frames of 1001 bits 35 /
+// 25, 256 of 2048 38 / 29, 512 of 4096 56 / 51).
+constexpr int kSplitMinItFew = 144;
+
+// Whether int8 frames of a K = 5, 7 rate-1/2 code run packed radix 4 where the
+// caller leaves the radix open: always but for few frames too short to be split
+// in time, which radix 2 runs faster: its wavefronts hold half as many frames
+// and a shorter chain per stage.  Forward and traceback, us, radix 2 / packed.
+// K = 7: one frame of 512 bits 17.2 / 19.9, 512 frames 19.4 / 23.2, 1024 20.2 /
+// 24.3, 1500 26.1 / 26.1; of 400 bits 1024 frames 19.4 / 21.2, 1500 23.9 / 22.8;
+// of 600 bits (split in two) one frame 20.6 / 19.5, 1024 26.2 / 26.1; of 1001
+// bits one 25.6 / 22.7, 512 31.7 / 27.5.  K = 5, whose packed wavefronts hold
+// eight frames, is near even below the line: one frame of 512 bits 16.2 / 17.1,
+// of 256 12.2 / 12.2, 4096 of 400 20.0 / 19.3; above it 5000 of 400 24.6 / 20.0,
+// one of 580 17.5 / 16.1.  The lines are one radix-2 wavefront per SIMD and the
+// shortest split frame.
+inline bool radix4_pays(int K, int cus, int64_t frames, int longest) {
+  return (frames << (K - 1)) / 64 > 4 * (int64_t)cus || longest >= 4 * kSplitMinItFew;
+}
+
 // Stages in a trip of the packed K = 8, 9 kernel (n = K - 1): parts of items
 // split in time begin at multiples of it.
 __host__ __device__ constexpr int wpk_period(int n) { return n == 8 ? 64 : 112; }

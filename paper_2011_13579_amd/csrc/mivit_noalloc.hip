@@ -54,8 +54,8 @@ constexpr int kMaxDevices = 64;
 
 __device__ __align__(256) uint8_t scratch[kScratchBytes + kTableBytes];
 
-// kernel families of the one-call path (the choices mivit_decode_uniform's
-// plans make for a uniform batch with default options)
+// kernel families of the one-call path (those of mivit_decode_uniform's plans,
+// whole frames, but for few short K = 5 int8 frames)
 enum : int { kFamRot2 = 0, kFamR4P = 1, kFamWide = 2 };
 constexpr int kRotModeDefault = 2;        // rotating kernel, exchanges in the VALU
 
@@ -71,7 +71,10 @@ struct Layout {
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 bool make_layout(const mivit_code& c, int dtype, int F, int S, int n_info, int cus, Layout& L) {
-  const bool packed = dtype == MIVIT_I8 && c.beta == 2 && (c.K == 5 || c.K == 7);
+  // (K = 5 always: here radix 2 took 14.5 us for one frame of 150 bits, packed
+  // 12.9; 64 of 200 16.2 and 15.4.  K = 7: 1 of 200 14.8 / 16.3, 64 of 512 20.9 / 25.1)
+  const bool packed = dtype == MIVIT_I8 && c.beta == 2 &&
+                      (c.K == 5 || (c.K == 7 && radix4_pays(c.K, cus, F, S)));
   L.fam = packed ? kFamR4P : (c.K <= 7 ? kFamRot2 : kFamWide);
   L.fpw = L.fam == kFamR4P ? 2 * (64 >> (c.K - 1)) : L.fam == kFamRot2 ? (64 >> (c.K - 1)) : 1;
   L.n_waves = (F + L.fpw - 1) / L.fpw;  // the wide kernel: one unit per frame (fpw 1)

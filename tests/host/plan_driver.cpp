@@ -333,7 +333,7 @@ int main() {
   same_kernel("k7_long", kK7, MIVIT_I8, 1, 600);
   same_kernel("k7_few", kK7, MIVIT_I8, 1024, 40);
   same_kernel("k7_many", kK7, MIVIT_I8, 1100, 40);
-  same_kernel("k5_few", kK5, MIVIT_I8, 4096, 40);
+  same_kernel("k5_long", kK5, MIVIT_I8, 1, 600);
   same_kernel("k5_many", kK5, MIVIT_I8, 4200, 40);
   same_kernel("k9_i8", kK9, MIVIT_I8, 3, 200);
   same_kernel("k9_f32", kK9, MIVIT_F32, 3, 200);

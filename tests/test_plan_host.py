@@ -92,3 +92,11 @@ def test_allocation_free_call_takes_what_its_limit_allows(out, name):
     traceback adds do not count, and end within the array."""
     assert out["noalloc_limit." + name] == "0 0"
     assert int(out["noalloc_room." + name]) <= 70 << 20
+
+
+@pytest.mark.parametrize("name,kernel", [
+    ("k7_short", "rot"), ("k7_long", "r4p"), ("k7_few", "rot"), ("k7_many", "r4p"),
+    ("k5_long", "r4p"), ("k5_many", "r4p"), ("k9_i8", "wpk1"), ("k9_f32", "wide4"),
+    ("k8_f32_many", "wide1")])
+def test_allocation_free_call_runs_the_plans_kernel(out, name, kernel):
+    assert out["same_kernel." + name] == "00 %s %s" % (kernel, kernel)
