@@ -169,10 +169,11 @@ __host__ __device__ constexpr int wpk_period(int n) { return n == 8 ? 64 : 112; 
 // stages in all whose longest frame has `longest`.  A lone frame's stages run
 // faster on several wavefronts, a full device wants one each (us, forward
 // pass, K = 9 rate 1/3, 1 / 2 / 4 wavefronts: one frame of 4096 bits
-// 235 / 178 / 175, 256 frames 246 / 186 / 181, 512 251 / 239 / 208, 1024
-// 257 / 253 / 278, 4096 of 2000 bits 344 / 394 / 487; K = 8, 1 / 2
-// wavefronts: 1 frame 130 / 116, 256 139 / 122, 1024 146 / 146): four up to
-// two wavefronts per SIMD, for K = 8 two below that.
+// 235 / 178 / 175, 256 frames 246 / 186 / 181, 512 251 / 239 / 208, 640 243 /
+// 227 / 217, 768 243 / 223 / 218, 896 244 / 236 / 250, 1024 257 / 253 / 278, 4096
+// of 2000 bits 344 / 394 / 487; K = 8, 1 / 2 wavefronts: 1 frame 130 / 116, 256
+// 139 / 122, 1024 146 / 146): four up to two wavefronts per SIMD (three would
+// still do for 640 and 768 frames), for K = 8 two below that.
 inline int wide_waves(int K, int cus, int64_t stages, int64_t longest) {
   const int64_t frames = longest > 0 ? (stages + longest - 1) / longest : 0;
   const int64_t simds = 4 * (int64_t)cus;
@@ -273,6 +274,11 @@ __device__ __forceinline__ uint32_t push_decision(uint32_t acc, uint64_t mask) {
          : "v"(acc), "s"(mask));
   return out;
 }
+
+// A grid of more workgroups of four wavefronts than the device has compute
+// units puts wavefronts on a SIMD together (all 256 of an MI355X; the rotation
+// below is a matter of time only, so a part of one may well use the same line).
+constexpr unsigned kComputeUnits = 256;
 
 // Wavefronts of equal work that share a SIMD should end together: the SIMD
 // serves the oldest first, so one of them runs ahead, ends early and leaves

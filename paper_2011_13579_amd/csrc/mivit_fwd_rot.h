@@ -797,7 +797,7 @@ __device__ __forceinline__ void fwd_rot_valu_wave(const DevCode* __restrict__ co
     T pm0 = F.pm;  // metrics entering the period from t0
     // Only where wavefronts share SIMDs, and for float32: 4096 frames of 8198
     // stages, decode, 416 -> 408 us; float16 took 376 against 369 with it.
-    const int slot = DT == 0 && gridDim.x > 256 ? wave_slot() : -1;
+    const int slot = DT == 0 && gridDim.x > kComputeUnits ? wave_slot() : -1;
     for (; t0 + SUPER <= F.S && F.bad == 0; t0 += SUPER) {
       pm0 = F.pm;
       valu_period<KM1, DT, BETA, 0, SUPER / 32>(F, t0);

@@ -160,9 +160,9 @@ __device__ __forceinline__ void frame_sync() {
 }
 
 
-// The larger of two metrics: v_max for floats too, so that the select does
-// not wait on the comparison's mask (no NaN arises: finite soft values, and
-// -inf plus finite branch metrics for unreachable float states).
+// The larger of two metrics; of a number and a NaN, the number.  (Floats come
+// here only from the loop for soft values that bring NaNs or infinities, and
+// the decision beside it compares, so a NaN candidate never wins.)
 __device__ __forceinline__ float tmax(float a, float b) { return __builtin_fmaxf(a, b); }
 __device__ __forceinline__ int tmax(int a, int b) { return a > b ? a : b; }
 

@@ -343,7 +343,7 @@ __global__ __launch_bounds__(64 * (WPF == 1 ? wide::kWideWaves : WPF), (1 << (KM
     for (int r = 0; r < R; ++r) pm0[r] = F.pm[r];
     // (only where wavefronts share SIMDs: K = 9, 1500 frames of 3000 bits 268
     // -> 250 us, K = 8, 4096 of 2000 180 -> 175)
-    const int slot = WPF == 1 && gridDim.x > 256 ? wave_slot() : -1;
+    const int slot = WPF == 1 && gridDim.x > kComputeUnits ? wave_slot() : -1;
     for (; t0 + W::TRIP <= F.S && F.bad == 0; t0 += W::TRIP) {
       if (slot >= 0) fair_share(slot, t0 / W::TRIP);
 #pragma unroll

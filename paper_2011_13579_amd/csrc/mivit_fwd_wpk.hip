@@ -418,7 +418,7 @@ __device__ __forceinline__ void unit(const DevCode& c, const Item& it, const Spl
     wave_sync();
     first<N, BETA, 0>(F);
     // (only where wavefronts share SIMDs)
-    const int slot = gridDim.x > 256 ? wave_slot() : -1;
+    const int slot = gridDim.x > kComputeUnits ? wave_slot() : -1;
     int t0 = t_s;
     for (; t0 < t_b; t0 += W::kTrip) trip<N, BETA, false, 0>(F, t0, lane);  // warm-up
     if (kind == 0 && U.part > 0) {

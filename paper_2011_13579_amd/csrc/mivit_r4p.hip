@@ -29,8 +29,8 @@
 // (the standard K = 7 code has w = 11; K = 5 has w <= 8), and for REN = 4 and
 // any K = 7 code.  (From a known start the other states stand below all that
 // n stages can make up, so range control waits until stage 8, when every
-// state has been reached; the start itself leaves room for that.)  The subtracted amounts are accumulated exactly and added
-// back to the final metric.
+// state has been reached; the start itself leaves room for that.)  The subtracted
+// amounts are accumulated exactly and added back to the final metric.
 //
 // Positions.  At time t (stages since the first iteration) state s has the
 // rotated index r = rotl_n(s, t mod n), so that stage t pairs the indices
@@ -487,7 +487,7 @@ __device__ __forceinline__ void fwd_pk_unit(const DevCode& c, const Item* __rest
       F.off0 = F.off1 = 0;
     };
     // (only where wavefronts share SIMDs)
-    const int slot = gridDim.x > 256 ? wave_slot() : -1;
+    const int slot = gridDim.x > kComputeUnits ? wave_slot() : -1;
     int t0 = t_s;
     for (; t0 < t_b; t0 += W::kTrip) trip<N, LB, REN, false, 0>(F, t0);  // warm-up: no stores
     if (kind == 0 && U.part > 0) {
@@ -582,6 +582,11 @@ __device__ __forceinline__ void fwd_pk_wave(const DevCode* __restrict__ codes,
 }
 
 constexpr int kPkWaves = 4;  // wavefronts per workgroup, one per SIMD (they share nothing)
+// Table buffers reserved per wavefront.  A pair per wavefront uses two; the room of
+// the third keeps its workgroups from crowding out those of other codes in a
+// mixed batch (10000 frames of K = 5, 7, 9: 609 us, 624 without it), and alone
+// it makes no difference.
+constexpr int kTblBufs = 3;
 
 // One wavefront per unit, or (counter != nullptr) a persistent grid whose
 // wavefronts take units in table order from a device counter that starts at
@@ -592,7 +597,7 @@ __global__ __launch_bounds__(64 * kPkWaves, N - LB == 2 ? 2 : 4) void k_fwd_pk(
     const SplitUnit* __restrict__ units, int n_units, R4Bound* bounds, int64_t* last_m,
     const int8_t* __restrict__ llr, uint64_t* __restrict__ surv, int64_t* metric,
     int32_t* end_out, int32_t* item_end, int32_t* counter) {
-  __shared__ __align__(16) uint32_t tbl_all[kPkWaves][3 * pk::Fwd<N, LB>::kBuf];
+  __shared__ __align__(16) uint32_t tbl_all[kPkWaves][kTblBufs * pk::Fwd<N, LB>::kBuf];
   const int wid = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   int u = __builtin_amdgcn_readfirstlane(blockIdx.x * kPkWaves + wid);
@@ -672,7 +677,7 @@ __global__ __launch_bounds__(64 * kPkWaves, N - LB == 2 ? 2 : 4) void k_pk_check
     R4Bound* bounds, const int64_t* __restrict__ last_m, int64_t* rep_m0,
     const int8_t* __restrict__ llr, uint64_t* __restrict__ surv, int64_t* metric,
     int32_t* end_out, int32_t* item_end) {
-  __shared__ __align__(16) uint32_t tbl_all[kPkWaves][3 * pk::Fwd<N, LB>::kBuf];
+  __shared__ __align__(16) uint32_t tbl_all[kPkWaves][kTblBufs * pk::Fwd<N, LB>::kBuf];
   const int wid = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int e = __builtin_amdgcn_readfirstlane(blockIdx.x * kPkWaves + wid);
   if (e >= n_split) return;  // no workgroup barriers: safe to leave

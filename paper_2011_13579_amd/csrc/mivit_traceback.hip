@@ -272,7 +272,7 @@ hipError_t launch_tb_seg(int layout, const DevCode* codes, const Item* items, in
 // packed radix 4) against about 35 VALU instructions and several branches
 // when bits were emitted one by one.  Bandwidth is the other bound: every
 // lane streams its warm-up as well as its segment, so a batch with enough
-// frames is cut into few, long segments (tb_plan).
+// frames is cut into few, long segments (tb_shape).
 //
 // kWords: rotating radix 2 (K <= 7), per 32 stages 2^n words, word p the
 //   decisions at position p, stage t at bit 31 - (t mod 32).
