@@ -360,13 +360,13 @@ def other_configs(torch, mv):
             alone["K%d" % cd.K] = round(_gpu_ms(torch, lambda: p1.decode(inputs[dt], *o1), 5), 3)
             p1.close()
         c4[dt]["parts_alone_ms"] = alone
-    # the longest frame alone (K=9 r1/3, 16346 stages): the float32 bound,
-    # with its states over one, two or four wavefronts
+    # the longest frame alone (K=9 r1/3, 16346 stages): the float32 bound, as a
+    # plan spreads it by itself and over two or four wavefronts
     lf9 = {}
     one9 = frm[int(np.argmax(S)):][:1].copy()
     assert codes[int(one9[0]["code"])] is CODE_K9
     one9["code"] = 0
-    for name, dt, var in (("f32_1wave", "f32", 0), ("f32_2waves", "f32", 6),
+    for name, dt, var in (("f32_default", "f32", 0), ("f32_2waves", "f32", 6),
                           ("f32_4waves", "f32", 7), ("i8_split", "i8", 0)):
         p1 = mv.Plan([CODE_K9], one9, dt, 2, variant=var)
         o1 = p1.empty_outputs(dev)

@@ -63,8 +63,10 @@
 // 3 - y of iteration 8G + k, frame h (0 = A, 1 = B) in bits
 // 16 (k & 1) + 8 h + 2 (k >> 1) and the bit above.
 //
-// What bounds it: vector issue (94% of the cycles while two wavefronts share
-// a SIMD); alone on a SIMD, LDS reads of the tables and range control besides.
+// What bounds it: vector issue; four states per lane take 40 instructions per
+// iteration, which is 74% of the issue cycles of the large batch's 200 us (two
+// wavefronts share a SIMD, and range control, table rows and the reads of the
+// entries leave gaps that two do not fill); one state per lane takes 12, 87%.
 // Measured, whole decode, against a kernel that took radix 4 in one step:
 // K = 7, 4096 frames of 8192 stages 312 -> 251 us (forward 246 -> 203);
 // 32768 x 2048 741 -> 540; 1 x 1024 52 -> 31; 2048 x 4096, one pair per
