@@ -1221,10 +1221,14 @@ mivit_status mivit_plan_describe(const mivit_plan* p, char* buf, int32_t len) {
   if (!p || !buf || len <= 0) return MIVIT_EINVAL;
   std::string s;
   for (const Part& q : p->parts) {
-    char line[256];
+    char line[320];
     for (const PlanGroup& g : q.groups) {
       // the rotating kernels run a wave table; the others one wavefront per item
       const bool table = g.kern == kKernRot2 || g.kern == kKernRot4P || g.kern == kKernRot4Q;
+      char spread[96];
+      std::snprintf(spread, sizeof spread,
+                    "%d wavefronts per item (automatic: one wavefront per item on a full device)",
+                    g.wpf);
       std::snprintf(line, sizeof line,
                     "%scode %d: K=%d beta=%d, %s forward, variant %d, %s, %d items, %d wavefronts",
                     s.empty() ? "" : "; ", q.code, g.K, g.beta, kern_name(g.kern), q.ch.variant,
@@ -1232,8 +1236,7 @@ mivit_status mivit_plan_describe(const mivit_plan* p, char* buf, int32_t len) {
                     : table        ? "one wavefront per table entry"
                     : q.ch.variant == 6 ? "two wavefronts per item"
                     : q.ch.variant == 7 ? "four wavefronts per item"
-                    : g.wpf == 2   ? "2 wavefronts per item (automatic)"
-                    : g.wpf == 4   ? "4 wavefronts per item (automatic)"
+                    : g.wpf > 1    ? spread
                     : g.two16      ? "one wavefront per item, two states per register"
                                    : "one wavefront per item",
                     g.count, table ? g.n_waves : g.wpf * g.count);

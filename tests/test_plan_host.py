@@ -73,11 +73,13 @@ def test_tuner_tries_every_form_of_the_float_kernel(out, name):
 
 
 @pytest.mark.parametrize("name,runs,text", [
-    ("k9_few", "wide4", "4 wavefronts per item (automatic), 4 items, 16 wavefronts"),
+    ("k9_few", "wide4", "4 wavefronts per item (automatic: one wavefront per item on a "
+     "full device), 4 items, 16 wavefronts"),
     ("k9_many", "wide1", "one wavefront per item, 4096 items, 4096 wavefronts"),
     ("k9_v6", "wide2", "two wavefronts per item, 4 items, 8 wavefronts"),
     ("k9_v7", "wide4", "four wavefronts per item, 4 items, 16 wavefronts"),
-    ("k8_few", "wide2", "2 wavefronts per item (automatic), 4 items, 8 wavefronts"),
+    ("k8_few", "wide2", "2 wavefronts per item (automatic: one wavefront per item on a "
+     "full device), 4 items, 8 wavefronts"),
     ("k8_f16", "wide1", "one wavefront per item, 4096 items, 4096 wavefronts")])
 def test_description_names_what_runs(out, name, runs, text):
     assert out["described." + name].startswith(runs + ": ")
